@@ -86,7 +86,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct Plan {
     int64_t n = 0, p = 0, npad = 0;
     int prec = 0, rchunks = 1;
-    size_t mean, scale, partial, xs, xt, hi, lo, S;
+    size_t mean, scale, partial, xs, xt, split, S;
     size_t wcnt, widx, wbeta, sigma, lam, cstat, esclist, bandcnt, bandidx;
     size_t suppcnt, suppidx, suppval, pendcnt, pendidx, dirtylist, esclist2, colinfo, polinfo;
     size_t wcnt64, widx64, wbeta64, sigma64, lam64, cstat64, esclist64;
@@ -138,8 +138,6 @@ Plan make_plan_data(int64_t n, int64_t p)
     L.scale = b.take(8 * P);
     L.partial = b.take(16 * (size_t)L.rchunks * P);
     L.xt = b.take(8 * N * P);
-    L.hi = b.take(2 * (size_t)L.npad * P);
-    L.lo = b.take(2 * (size_t)L.npad * P);
     L.pool_cap = std::min<int64_t>(p * p, 32 * p + 65536);
     const size_t lists = P * kWMax + (size_t)L.pool_cap;
     L.wcnt = b.take(4 * P);
@@ -199,14 +197,16 @@ Plan make_plan_g(int64_t n, int64_t p, int prec, int G)
     Bump b;
     L.mean = b.take(8 * P);
     L.scale = b.take(8 * P);
-    L.partial = b.take(16 * (size_t)L.rchunks * P);
-    L.xs = L.xt = L.hi = L.lo = 0;
+    L.partial = L.xs = L.xt = L.split = 0;
+    if (prec != SPMESL_MIXED) L.partial = b.take(16 * (size_t)L.rchunks * P);
     if (prec == SPMESL_FP64) L.xs = b.take(8 * N * P);
     if (prec == SPMESL_FP32) L.xs = b.take(4 * N * P);
     if (prec == SPMESL_MIXED) {
         L.xt = b.take(8 * N * P);
-        L.hi = b.take(2 * (size_t)L.npad * P);
-        L.lo = b.take(2 * (size_t)L.npad * P);
+        // the statistics' partial sums (16 rchunks p bytes, rchunks at most
+        // (n + 7) / 8) are read before Xt is written over them
+        L.partial = L.xt;
+        L.split = b.take(2 * (size_t)split_size(p, L.npad));
     }
     L.S = b.take(tsz * P * P);
     // per-column lists hold kWMax entries each; the dense tier's longer
@@ -759,7 +759,7 @@ static void enqueue_standardize(const Plan &L, const spmesl_problem *prob, char 
     double *scale = (double *)(ws + L.scale);
     if (L.prec == SPMESL_MIXED &&
         launch_stats_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt),
-                           (uint16_t *)(ws + L.hi), (uint16_t *)(ws + L.lo), L.npad, &dctl->flags,
+                           (uint16_t *)(ws + L.split), L.npad, &dctl->flags,
                            (int *)(ws + L.pendcnt), s)) {
         mark(mk, s, "standardize");
         return;
@@ -773,7 +773,7 @@ static void enqueue_standardize(const Plan &L, const spmesl_problem *prob, char 
         launch_standardize_f32(prob->X, n, p, prob->ldx, mean, scale, (float *)(ws + L.xs), s);
     else
         launch_standardize_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt),
-                                 (uint16_t *)(ws + L.hi), (uint16_t *)(ws + L.lo), L.npad, s);
+                                 (uint16_t *)(ws + L.split), L.npad, s);
     mark(mk, s, "standardize");
 }
 
@@ -992,8 +992,7 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
     else if (L.prec == SPMESL_FP32)
         launch_syrk_f32((const float *)(ws + L.xs), n, p, (float *)(ws + L.S), sc, s);
     else
-        launch_syrk_bf16x3((const uint16_t *)(ws + L.hi), (const uint16_t *)(ws + L.lo), n, L.npad,
-                           p, (float *)(ws + L.S), sc, s);
+        launch_syrk_bf16x3((const uint16_t *)(ws + L.split), n, L.npad, p, (float *)(ws + L.S), sc, s);
     mark(mk, s, L.prec == SPMESL_FP64 ? "syrk_f64" : (L.prec == SPMESL_FP32 ? "syrk_f32" : "syrk_bf16x3"));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[2], s));
 
@@ -1077,12 +1076,11 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
     mark(mk, s, nullptr);
     launch_zero_words((uint32_t *)dctl, sizeof(Ctl) / 4, s);
     mark(mk, s, "zero_control");
-    if (!launch_stats_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt), (uint16_t *)(ws + L.hi),
-                            (uint16_t *)(ws + L.lo), L.npad, &dctl->flags, (int *)(ws + L.pendcnt), s)) {
+    if (!launch_stats_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt), nullptr, L.npad,
+                            &dctl->flags, (int *)(ws + L.pendcnt), s)) {
         launch_colstats(prob->X, n, p, prob->ldx, (double *)(ws + L.partial), L.rchunks, mean, scale,
                         &dctl->flags, (int *)(ws + L.pendcnt), s);
-        launch_standardize_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt),
-                                 (uint16_t *)(ws + L.hi), (uint16_t *)(ws + L.lo), L.npad, s);
+        launch_standardize_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt), nullptr, L.npad, s);
     }
     mark(mk, s, "standardize");
     const int v0 = fork_output_fill(ctx, res, p, s, mk);
@@ -1366,7 +1364,7 @@ static int fork_batch_fill(spmesl_ctx *ctx, int count, const spmesl_result *res,
 struct BatchGrids {
     int64_t cols = 0, tiles = 0, kkt_blocks = 0, pmax = 0;
     int rj = 4;
-    int syrk_edge = 64;  // covariance tile edge of the double and float forms
+    int syrk_edge = 64;  // covariance tile edge
 };
 
 static void limits_of(const spmesl_options *opt, int *max_outer, int *max_sweeps, int *max_rounds)
@@ -1402,15 +1400,17 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_op
     Ctl *dctl = (Ctl *)(ws0 + B.ctl_off);
     BatchGrids gr;
     for (int i = 0; i < count; ++i) gr.rj = std::min(gr.rj, kkt_rows_for<T>(plans[(size_t)i].p, 0, tu));
-    if (sizeof(T) == 8) {
-        // 128 x 128 double tiles when the batch's tiles of that edge fill the
-        // chip (the same rule as one problem's, on the batch's total)
-        int64_t t128 = 0;
+    {
+        // the large tiles by the same rules as one problem's, on the batch's
+        // total of them
+        const int64_t big = sizeof(T) == 8 ? 128 : 256;
+        int64_t nbig = 0;
         for (int i = 0; i < count; ++i) {
-            const int64_t e = (plans[(size_t)i].p + 127) / 128;
-            t128 += e * (e + 1) / 2;
+            const int64_t e = (plans[(size_t)i].p + big - 1) / big;
+            nbig += e * (e + 1) / 2;
         }
-        gr.syrk_edge = t128 >= 256 ? 128 : 64;
+        if (sizeof(T) == 8) gr.syrk_edge = nbig >= 256 ? 128 : 64;
+        else if (plans[0].prec == SPMESL_MIXED) gr.syrk_edge = syrk_bf16x3_edge(nbig);
     }
     auto *first = (ColArgs<T> *)(h + t.first);
     auto *resume = (ColArgs<T> *)(h + t.resume);
@@ -1430,8 +1430,8 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_op
         int64_t tiles = 0, blocks = 0;
         if (L.prec == SPMESL_MIXED)
             ((SyrkJob *)(h + t.syrk))[i] =
-                syrk_job_bf16x3((const uint16_t *)(ws + L.hi), (const uint16_t *)(ws + L.lo), L.n, L.npad, L.p,
-                                (float *)(ws + L.S), sc, &tiles);
+                syrk_job_bf16x3((const uint16_t *)(ws + L.split), L.n, L.npad, L.p, (float *)(ws + L.S), sc,
+                                gr.syrk_edge, &tiles);
         else
             ((SyrkJobT<T> *)(h + t.syrk))[i] =
                 syrk_job_mfma<T>((const T *)(ws + L.xs), L.n, L.p, (T *)(ws + L.S), sc, gr.syrk_edge, &tiles);
@@ -1489,7 +1489,7 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     if (v != SPMESL_OK) return v;
     if (mixed)
         launch_syrk_bf16x3_grouped((const SyrkJob *)(tb + t.syrk), (const int64_t *)(tb + t.tile_off), count,
-                                   gr.tiles, s);
+                                   gr.tiles, gr.syrk_edge, s);
     else
         launch_syrk_mfma_grouped<T>((const SyrkJobT<T> *)(tb + t.syrk), (const int64_t *)(tb + t.tile_off), count,
                                     gr.tiles, gr.syrk_edge, s);
@@ -2076,9 +2076,8 @@ int spmesl_covariance(spmesl_ctx *ctx, const spmesl_problem *prob, int precision
         launch_syrk_f32((const float *)(ws + L.xs), n, p, (float *)S_out, Screen{}, s);
     } else {
         launch_standardize_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt),
-                                 (uint16_t *)(ws + L.hi), (uint16_t *)(ws + L.lo), L.npad, s);
-        launch_syrk_bf16x3((const uint16_t *)(ws + L.hi), (const uint16_t *)(ws + L.lo), n, L.npad, p,
-                           (float *)S_out, Screen{}, s);
+                                 (uint16_t *)(ws + L.split), L.npad, s);
+        launch_syrk_bf16x3((const uint16_t *)(ws + L.split), n, L.npad, p, (float *)S_out, Screen{}, s);
     }
     HIPTRY(ctx, hipGetLastError());
     v = ensure_pinned(ctx, 1);

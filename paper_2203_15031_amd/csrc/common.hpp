@@ -157,18 +157,32 @@ void launch_standardize_f64(const double *X, int64_t n, int64_t p, int64_t ldx,
 // float copy of the standardised data, n x p row-major.
 void launch_standardize_f32(const double *X, int64_t n, int64_t p, int64_t ldx,
                             const double *mean, const double *scale, float *Xs, hipStream_t s);
-// Transposed standardised data for the mixed form: Xt (p x n double) and
-// the two-term bfloat16 split hi/lo of float(x), p x npad (npad = n padded
-// to a multiple of 32, zero-filled).
+// The two-term bfloat16 split x = hi + lo of the standardised data (as
+// float), in the operand order of the 16 x 16 x 32 matrix instructions:
+// blocks of 16 variables x 32 samples, the hi block and then the lo block,
+// each as 64 lanes of 8 values (lane l: variable l % 16, samples
+// 8 (l / 16) ..).  Samples are zero-padded to npad (a multiple of 64); the
+// variables that pad the last block of 16 are never written, and products
+// with them are never stored.  Position (in values) of the 8 values of
+// variable v at samples 8q .. 8q + 7, part 0 (hi) or 1 (lo).
+__host__ __device__ __forceinline__ int64_t split_offset(int64_t v, int64_t q, int64_t npad, int part)
+{
+    return (((v >> 4) * (npad >> 5) + (q >> 2)) * 2 + part) * 512 + (((q & 3) << 4) + (v & 15)) * 8;
+}
+// values of the whole split
+inline int64_t split_size(int64_t p, int64_t npad) { return (p + 15) / 16 * 16 * npad * 2; }
+
+// Transposed standardised data for the mixed form: Xt (p x n double) and the
+// split (null: not written).
 // Mixed form: column statistics and the split in one kernel (X read once).
 // Returns false (nothing launched) when a strip of n samples does not fit
 // the kernel's LDS budget; the caller then takes the two-kernel path.
 bool launch_stats_split(const double *X, int64_t n, int64_t p, int64_t ldx, double *mean,
-                        double *scale, double *Xt, uint16_t *hi, uint16_t *lo, int64_t npad,
+                        double *scale, double *Xt, uint16_t *split, int64_t npad,
                         int *flags, int *zero_cnt, hipStream_t s);
 void launch_standardize_split(const double *X, int64_t n, int64_t p, int64_t ldx,
                               const double *mean, const double *scale, double *Xt,
-                              uint16_t *hi, uint16_t *lo, int64_t npad, hipStream_t s);
+                              uint16_t *split, int64_t npad, hipStream_t s);
 
 // S = Xs^T Xs / n with unit diagonal (p x p row-major, full).
 // Screen of the first solves, done where S is written: for every column k
@@ -184,8 +198,8 @@ struct Screen {
 };
 void launch_syrk_f64(const double *Xs, int64_t n, int64_t p, double *S, const Screen &sc, hipStream_t s);
 void launch_syrk_f32(const float *Xs, int64_t n, int64_t p, float *S, const Screen &sc, hipStream_t s);
-void launch_syrk_bf16x3(const uint16_t *hi, const uint16_t *lo, int64_t n, int64_t npad,
-                        int64_t p, float *S, const Screen &sc, hipStream_t s);
+void launch_syrk_bf16x3(const uint16_t *split, int64_t n, int64_t npad, int64_t p, float *S, const Screen &sc,
+                        hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Grouped launches: one launch runs the same step of many problems (the
@@ -209,7 +223,7 @@ void launch_group_offsets(const int *cnt, int64_t stride, int nd, int64_t *off, 
 
 // One problem's covariance tiles (the mixed form's kernel).
 struct SyrkJob {
-    const uint16_t *hi, *lo;
+    const uint16_t *split;
     int64_t npad, p;
     float *S;
     int Tt;
@@ -234,9 +248,12 @@ SyrkJobT<T> syrk_job_mfma(const T *Xs, int64_t n, int64_t p, T *S, const Screen 
 template <typename T>
 void launch_syrk_mfma_grouped(const SyrkJobT<T> *tab, const int64_t *tile_off, int nd, int64_t tiles, int edge,
                               hipStream_t s);
-SyrkJob syrk_job_bf16x3(const uint16_t *hi, const uint16_t *lo, int64_t n, int64_t npad, int64_t p, float *S,
-                        const Screen &sc, int64_t *tiles);
-void launch_syrk_bf16x3_grouped(const SyrkJob *tab, const int64_t *tile_off, int nd, int64_t tiles,
+// Tile edge of the mixed form's kernel (256 or 64) from the number of
+// 256 x 256 tiles of the launch.
+int syrk_bf16x3_edge(int64_t tiles256);
+SyrkJob syrk_job_bf16x3(const uint16_t *split, int64_t n, int64_t npad, int64_t p, float *S, const Screen &sc,
+                        int edge, int64_t *tiles);
+void launch_syrk_bf16x3_grouped(const SyrkJob *tab, const int64_t *tile_off, int nd, int64_t tiles, int edge,
                                 hipStream_t s);
 
 // Per-column working-set scaled lasso (see colsolve.hip).

@@ -156,14 +156,33 @@ __device__ __forceinline__ uint16_t bf16_bits(float f)
 
 __device__ __forceinline__ float bf16_value(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+// Split of 8 consecutive samples of one variable, one 16-byte store each for
+// hi and lo.
+__device__ __forceinline__ void store_split8(uint16_t *__restrict__ split, int64_t v, int64_t q, int64_t npad,
+                                             const float (&f)[8])
+{
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint16_t h0 = bf16_bits(f[2 * e]), h1 = bf16_bits(f[2 * e + 1]);
+        const uint16_t l0 = bf16_bits(f[2 * e] - bf16_value(h0)), l1 = bf16_bits(f[2 * e + 1] - bf16_value(h1));
+        h[e] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        l[e] = (uint32_t)l0 | ((uint32_t)l1 << 16);
+    }
+    *reinterpret_cast<u4 *>(split + split_offset(v, q, npad, 0)) = u4{h[0], h[1], h[2], h[3]};
+    *reinterpret_cast<u4 *>(split + split_offset(v, q, npad, 1)) = u4{l[0], l[1], l[2], l[3]};
+}
+
 // Transposing standardisation for the mixed form.  Block: 64 (j) x 4 (i
-// lanes); tile 64 samples x 64 variables staged through LDS so that both
-// the read of X (rows) and the writes of Xt/hi/lo (variable-major) are
-// coalesced.
+// lanes); tile 64 samples x 64 variables staged through LDS so that the read
+// of X (rows), the writes of Xt (variable-major) and those of the split
+// (16 variables x 16 bytes) are coalesced.
 __global__ __launch_bounds__(256) void k_standardize_split(
     const double *__restrict__ X, int64_t n, int64_t p, int64_t ldx,
     const double *__restrict__ mean, const double *__restrict__ scale, double *__restrict__ Xt,
-    uint16_t *__restrict__ hi, uint16_t *__restrict__ lo, int64_t npad)
+    uint16_t *__restrict__ split, int64_t npad)
 {
     __shared__ double tile[64][65];
     int64_t i0 = (int64_t)blockIdx.x * 64;
@@ -181,15 +200,18 @@ __global__ __launch_bounds__(256) void k_standardize_split(
         int64_t jj = j0 + v;
         int64_t ii = i0 + tx;
         if (jj >= p) continue;
-        double x = tile[tx][v];
-        if (ii < n) Xt[jj * n + ii] = x;
-        if (ii < npad) {
-            float f = (float)x;
-            uint16_t h = bf16_bits(f);
-            uint16_t l = bf16_bits(f - bf16_value(h));
-            hi[jj * npad + ii] = ii < n ? h : (uint16_t)0;
-            lo[jj * npad + ii] = ii < n ? l : (uint16_t)0;
-        }
+        if (ii < n) Xt[jj * n + ii] = tile[tx][v];
+    }
+    if (!split) return;
+    // 64 variables x 8 groups of 8 samples (the tile is zero past n, and npad
+    // is a multiple of 64)
+    for (int e = threadIdx.x; e < 512; e += 256) {
+        const int v = e & 63, q = e >> 6;
+        if (j0 + v >= p) continue;
+        float f[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) f[u] = (float)tile[8 * q + u][v];
+        store_split8(split, j0 + v, i0 / 8 + q, npad, f);
     }
 }
 
@@ -197,13 +219,14 @@ __global__ __launch_bounds__(256) void k_standardize_split(
 // strip of SW variables over all n samples: the strip is read once into LDS
 // (coalesced rows of SW doubles), the column means and centred sums of
 // squares are taken from LDS in two passes in a fixed order, and the same
-// block writes Xt and the bf16 split variable-major.  It also zeroes the
-// strip's screen counters (the covariance kernel appends to them).
+// block writes Xt (variable-major) and the bf16 split (operand order).  It
+// also zeroes the strip's screen counters (the covariance kernel appends to
+// them).
 template <int SW>
 __global__ __launch_bounds__(256) void k_stats_split(const double *__restrict__ X, int64_t n, int64_t p,
                                                      int64_t ldx, double *__restrict__ mean,
                                                      double *__restrict__ scale, double *__restrict__ Xt,
-                                                     uint16_t *__restrict__ hi, uint16_t *__restrict__ lo,
+                                                     uint16_t *__restrict__ split,
                                                      int64_t npad, int *__restrict__ flags,
                                                      int *__restrict__ zero_cnt)
 {
@@ -265,14 +288,19 @@ __global__ __launch_bounds__(256) void k_stats_split(const double *__restrict__ 
         const int64_t jj = j0 + w;
         if (jj >= p) break;
         const double mm = mv[w], cc = cv[w];
-        for (int64_t i = t; i < npad; i += 256) {
-            const double x = i < n ? (strip[i * SWP + w] - mm) * cc : 0.0;
-            if (i < n) Xt[jj * n + i] = x;
-            const float f = (float)x;
-            const uint16_t h = bf16_bits(f);
-            hi[jj * npad + i] = h;
-            lo[jj * npad + i] = bf16_bits(f - bf16_value(h));
+        for (int64_t i = t; i < n; i += 256) Xt[jj * n + i] = (strip[i * SWP + w] - mm) * cc;
+    }
+    if (!split || j >= p) return;
+    // the thread's variable, groups of 8 samples g, g + G, ..
+    const double mm = mv[v], cc = cv[v];
+    for (int64_t q = g; q < npad / 8; q += G) {
+        float f[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t i = 8 * q + u;
+            f[u] = i < n ? (float)((strip[i * SWP + v] - mm) * cc) : 0.0f;
         }
+        store_split8(split, j, q, npad, f);
     }
 }
 
@@ -288,7 +316,7 @@ static int stats_split_width(int64_t n)
 }
 
 bool launch_stats_split(const double *X, int64_t n, int64_t p, int64_t ldx, double *mean,
-                        double *scale, double *Xt, uint16_t *hi, uint16_t *lo, int64_t npad,
+                        double *scale, double *Xt, uint16_t *split, int64_t npad,
                         int *flags, int *zero_cnt, hipStream_t s)
 {
     const int sw = stats_split_width(n);
@@ -297,20 +325,20 @@ bool launch_stats_split(const double *X, int64_t n, int64_t p, int64_t ldx, doub
     const unsigned blocks = (unsigned)((p + sw - 1) / sw);
     if (sw == 8)
         hipLaunchKernelGGL(k_stats_split<8>, dim3(blocks), dim3(256), lds, s, X, n, p, ldx, mean, scale,
-                           Xt, hi, lo, npad, flags, zero_cnt);
+                           Xt, split, npad, flags, zero_cnt);
     else
         hipLaunchKernelGGL(k_stats_split<4>, dim3(blocks), dim3(256), lds, s, X, n, p, ldx, mean, scale,
-                           Xt, hi, lo, npad, flags, zero_cnt);
+                           Xt, split, npad, flags, zero_cnt);
     return true;
 }
 
 void launch_standardize_split(const double *X, int64_t n, int64_t p, int64_t ldx,
                               const double *mean, const double *scale, double *Xt,
-                              uint16_t *hi, uint16_t *lo, int64_t npad, hipStream_t s)
+                              uint16_t *split, int64_t npad, hipStream_t s)
 {
     dim3 g((unsigned)((npad + 63) / 64), (unsigned)((p + 63) / 64));
     hipLaunchKernelGGL(k_standardize_split, g, dim3(256), 0, s, X, n, p, ldx, mean, scale, Xt,
-                       hi, lo, npad);
+                       split, npad);
 }
 
 __global__ __launch_bounds__(256) void k_pack_columns(const double *__restrict__ X, int64_t n, int64_t p,

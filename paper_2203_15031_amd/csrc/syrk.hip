@@ -200,16 +200,36 @@ __device__ __forceinline__ int64_t xcd_order(int64_t nb, int64_t bid)
     return x * q + (x < r ? x : r) + (bid >> 3);
 }
 
-// Upper-triangle tile t (bj <= bk, row by row) of a T x T tiling.
+// Upper-triangle tile t (bj <= bk) of a T x T tiling, in strips of kStrip
+// tile rows taken column by column: the tiles an XCD runs at a time (64 at
+// two blocks per CU) then share 8 row and 8 column panels in its L2, where
+// row by row they shared one row panel and streamed 64 column panels.
+constexpr int kStrip = 8;
 __device__ __forceinline__ void tri_tile(int T, int64_t t, int *bj, int *bk)
 {
-    int row = 0;
-    while (t >= T - row) {
-        t -= T - row;
-        ++row;
+    int r0 = 0;
+    for (;;) {
+        const int h = T - r0 < kStrip ? T - r0 : kStrip;  // rows of the strip
+        const int64_t cnt = (int64_t)h * (T - r0) - (int64_t)h * (h - 1) / 2;
+        if (t < cnt || r0 + h >= T) {
+            // the first h columns of the strip hold 1, 2, .., h tiles
+            int c = 0;
+            while (c < h - 1 && t > c) {
+                t -= c + 1;
+                ++c;
+            }
+            if (c == h - 1) {
+                *bk = r0 + c + (int)(t / h);
+                *bj = r0 + (int)(t % h);
+            } else {
+                *bk = r0 + c;
+                *bj = r0 + (int)t;
+            }
+            return;
+        }
+        t -= cnt;
+        r0 += h;
     }
-    *bj = row;
-    *bk = row + (int)t;
 }
 
 // Map a linear block id to an upper-triangle tile, XCD-aware.
@@ -602,187 +622,311 @@ void launch_syrk_f32(const float *Xs, int64_t n, int64_t p, float *S, const Scre
 }
 
 // ---------------------------------------------------------------------------
-// mixed form: bf16 split, 256 x 256 tiles, 32 samples per stage
+// mixed form: bf16 split, operands in the order of split_offset (the 64 lanes
+// of a wave read one 16 x 32 operand of hi or lo as 1 KB of consecutive
+// memory or LDS, 16 bytes per lane, without bank conflicts)
 //
-// A block of 8 waves (64 x 128 each) computes one 256 x 256 tile; blocks
-// loop over the upper-triangle tile list when it is longer than the grid.
-// A stage (hi and lo of the tile's 256 row and 256 column variables over 32
-// samples, 64 KB) is copied to LDS by the direct global-to-LDS path into two
-// alternating buffers, so the copy of stage s + 1 is in flight while stage s
-// feeds the matrix cores.  Against 128 x 128 tiles this halves the panel
-// traffic per flop; measured at p = 5000 it takes 64 us where the 128 x 128
-// form at two blocks per CU took 85 us and the register-staged form 103 us.
-//
-// LDS layout of a panel: row m (a variable) holds its 32 samples as four
-// 16-byte chunks, chunk c in slot c ^ f(m), f(m) = ((m >> 1) ^ (m >> 2)) & 3.
-// The operand reads (16 lanes on 16 consecutive rows, one chunk each) then
-// touch distinct banks with either 32 or 64 LDS banks.
-//
-// The epilogue writes S from the accumulators, directly (64-byte row
-// segments) and transposed (16-byte stores of four consecutive columns),
-// with no LDS staging; the screen of the first solves is taken on the same
-// values (each pair for both columns).
+// Both kernels give every entry its products in the same order (per 32
+// samples lo hi, hi lo, hi hi), so S is the same to the bit whichever runs.
 // ---------------------------------------------------------------------------
+constexpr int kBfKC = 32;  // samples per step (one MFMA k-step)
+
+__device__ __forceinline__ f4 bf_mma(bf8 ha, bf8 la, bf8 hb, bf8 lb, f4 c)
+{
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(la, hb, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha, lb, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha, hb, c, 0, 0, 0);
+}
+
+template <bool NT, typename V> __device__ __forceinline__ void store_s(V *at, V v)
+{
+    if constexpr (NT) __builtin_nontemporal_store(v, at);
+    else *at = v;
+}
+
+// A wave's NA x NB accumulator blocks (from variable j0 / k0 of S) to S and
+// the screen, straight from the accumulators: lane l holds rows jb .. jb + 3
+// (jb = 4 (l / 16) within the 16 x 16 block) of column kk = l % 16.  Direct:
+// 16 lanes store 64 consecutive bytes of a row of S; mirrored: the lane's
+// four rows are four consecutive columns of row kk, one 16-byte store.  A
+// diagonal tile stores its upper triangle both ways, so S is symmetric bit
+// for bit.  Returns the wave's count of screen entries.
+// NT: nontemporal stores.
+template <int NA, int NB, bool NT, typename SCR>
+__device__ __forceinline__ int bf_store(const f4 (&acc)[NA][NB], float *__restrict__ S, int64_t p, int64_t j0,
+                                        int64_t k0, bool diag, float invn, float thr, int *__restrict__ scnt,
+                                        int *__restrict__ sidx, SCR &scr, int w)
+{
+    const int lane = threadIdx.x & 63;
+    const int g4 = 4 * (lane >> 4), c16 = lane & 15;
+    const bool vec_ok = (p & 3) == 0;  // rows of S 16-byte aligned
+    int nscr = 0;
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int64_t kk = k0 + 16 * b + c16;
+            const int64_t jb = j0 + 16 * a + g4;
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = jb + r == kk ? 1.0f : acc[a][b][r] * invn;
+            // screen: a pair above the threshold is a candidate of both
+            // columns (every lane takes part in the ballots)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool mine = jb + r < p && kk < p && (!diag || jb + r < kk);
+                screen_pair_wave(scr, w, nscr, scnt, sidx, thr, jb + r, kk, mine ? v[r] : 0.0f);
+            }
+            if (kk >= p) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (jb + r < p && (!diag || jb + r <= kk)) store_s<NT>(&S[(jb + r) * p + kk], v[r]);
+            if (vec_ok && jb + 3 < p && (!diag || kk > jb + 3)) {
+                store_s<NT>(reinterpret_cast<f4 *>(&S[kk * p + jb]), f4{v[0], v[1], v[2], v[3]});
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (jb + r < p && (!diag || kk > jb + r)) store_s<NT>(&S[kk * p + jb + r], v[r]);
+            }
+        }
+    return nscr;
+}
+
+// --- 64 x 64 tiles: operands straight into registers ----------------------
+// A block of four waves, each its own 32 x 32 quarter, with no LDS staging
+// and no barrier: a wave keeps the loads of the next three steps (8 operands
+// each) in flight behind the 12 matrix-core operations of the current one.
+// Small p is bound by the latency of one tile: 25 -> 5.3 us at n = 100,
+// p = 200, 37 -> 6.6 at n = 250, p = 500 and 98 -> 33 at n = 1000, p = 2000
+// against 256 x 256 tiles (1, 3 and 36 of them).
+constexpr int kBfSmall = 64;
+typedef ScreenWaves<4, 448> BfScreen64;
+
+__device__ __forceinline__ void bf_tile64(const uint16_t *__restrict__ split, int64_t npad, int64_t p,
+                                          float *__restrict__ S, float invn, float thr, int *__restrict__ scnt,
+                                          int *__restrict__ sidx, int bj, int bk, BfScreen64 &scr)
+{
+    constexpr int NB = 2, D = 4;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int wm = w & 1, wn = w >> 1;
+    const int ks = (int)(npad / kBfKC);
+    const int64_t j0 = (int64_t)bj * kBfSmall + 32 * wm, k0 = (int64_t)bk * kBfSmall + 32 * wn;
+    const bool diag = bj == bk;
+    int nscr = 0;
+    // the wave below the diagonal of a diagonal tile has nothing to store,
+    // nor has one past the last variable
+    if (j0 < p && k0 < p && !(diag && wm > wn)) {
+        const int64_t rbs = (p + 15) / 16;
+        const bf8 *pa[NB], *pb[NB];
+#pragma unroll
+        for (int a = 0; a < NB; ++a) {
+            // row blocks past the last load that one (never stored)
+            const int64_t ra = j0 / 16 + a, rb = k0 / 16 + a;
+            pa[a] = reinterpret_cast<const bf8 *>(split) + (ra < rbs ? ra : rbs - 1) * ks * 128 + lane;
+            pb[a] = reinterpret_cast<const bf8 *>(split) + (rb < rbs ? rb : rbs - 1) * ks * 128 + lane;
+        }
+        f4 acc[NB][NB];
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[a][b] = f4{0, 0, 0, 0};
+        bf8 ha[D][NB], la[D][NB], hb[D][NB], lb[D][NB];
+        auto load = [&](int st, int d) {
+            const int64_t o = (int64_t)(st < ks ? st : ks - 1) * 128;
+#pragma unroll
+            for (int a = 0; a < NB; ++a) {
+                ha[d][a] = pa[a][o];
+                la[d][a] = pa[a][o + 64];
+                hb[d][a] = pb[a][o];
+                lb[d][a] = pb[a][o + 64];
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d) load(d, d);
+        for (int s0 = 0; s0 < ks; s0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                load(s0 + d + D - 1, (d + D - 1) % D);
+                if (s0 + d < ks) {
+#pragma unroll
+                    for (int a = 0; a < NB; ++a)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+                            acc[a][b] = bf_mma(ha[d][a], la[d][a], hb[d][b], lb[d][b], acc[a][b]);
+                }
+            }
+        }
+        nscr = bf_store<NB, NB, false>(acc, S, p, j0, k0, diag, invn, thr, scnt, sidx, scr, w);
+    }
+    if (lane == 0) scr.n[w] = nscr;
+    __syncthreads();
+    screen_flush_waves(scr, scnt, sidx);
+}
+
+__global__ __launch_bounds__(256) void k_syrk_bf16x3_64(const uint16_t *__restrict__ split, int64_t npad, int64_t p,
+                                                        float *__restrict__ S, int Tt, float invn, float thr,
+                                                        int *__restrict__ scnt, int *__restrict__ sidx)
+{
+    __shared__ BfScreen64 scr;
+    int bj, bk;
+    tile_of_block(Tt, &bj, &bk);
+    bf_tile64(split, npad, p, S, invn, thr, scnt, sidx, bj, bk, scr);
+}
+
+// The tiles of many problems in one launch: block b (in the XCD-aware order)
+// is tile b - off[d] of problem d.
+__global__ __launch_bounds__(256) void k_syrk_bf16x3_64_grouped(const SyrkJob *__restrict__ tab,
+                                                                const int64_t *__restrict__ off, int nd)
+{
+    __shared__ BfScreen64 scr;
+    const int64_t g = xcd_order(gridDim.x, blockIdx.x);
+    const int d = group_of(off, nd, g);
+    const SyrkJob &J = tab[d];
+    int bj, bk;
+    tri_tile(J.Tt, g - off[d], &bj, &bk);
+    bf_tile64(J.split, J.npad, J.p, J.S, J.invn, J.thr, J.scnt, J.sidx, bj, bk, scr);
+}
+
+// --- 256 x 256 tiles: two LDS stages, operands one block ahead -------------
+// A block of 8 waves (64 x 128 each); a stage holds the operands of 32
+// samples of the tile's 256 row and 256 column variables (64 KB, copied by
+// the direct global-to-LDS path).  Within a stage a wave keeps the operands
+// of the next column block in flight behind the 12 matrix-core operations of
+// the current one.  The one barrier of a stage stands before its last two
+// column blocks, whose operands are already in registers: past it every wave
+// is done with the stage's LDS, the next stage's copies (issued a whole
+// stage earlier) have landed, the copies after that are issued into the
+// freed buffer, and the first operands of the next stage are read behind the
+// remaining 24 operations.  Reading all operands of a stage behind its
+// barrier took 61 us at n = 400, p = 5000 and 1462 at n = 1000, p = 20000
+// (no screen); this order takes 53.5 and 1310 (3 n p^2 bf16 operations in
+// the latter: 0.92 PFLOP/s), the stores of S being about a third of it.
 constexpr int kBfTile = 256;
-constexpr int kBfKC = 32;                     // samples per stage (one MFMA k-step)
-constexpr int kBfPanel = kBfTile * kBfKC * 2; // 16 KB: 256 rows x 64 B
-constexpr int kBfStage = 4 * kBfPanel;        // hi_J, lo_J, hi_K, lo_K
-typedef ScreenWaves<8, 448> BfScreen;        // fills the LDS left by the two stages
+constexpr int kBfPanel = kBfTile * kBfKC * 4;  // 32 KB: 16 blocks of 16 variables, hi and lo
+constexpr int kBfStage = 2 * kBfPanel;
+typedef ScreenWaves<8, 448> BfScreen;          // fills the LDS left by the two stages
 constexpr int kBfLds = 2 * kBfStage + (int)sizeof(BfScreen);
 static_assert(kBfLds <= 160 * 1024, "LDS of one block");
 
-__device__ __forceinline__ int bf_swz(int m) { return ((m >> 1) ^ (m >> 2)) & 3; }
-
-// Upper-triangle tile number -> (row block, column block), row-major order.
-__device__ __forceinline__ void bf_tile(int t, int T, int *bj, int *bk)
-{
-    int row = 0;
-    while (t >= T - row) {
-        t -= T - row;
-        ++row;
-    }
-    *bj = row;
-    *bk = row + t;
-}
-
-// Issue the copies of one stage: samples [i0, i0 + 32) of variables j0.. and
-// k0.. (hi and lo).  A diagonal tile copies its one panel pair only.  Rows
-// past p load row p - 1 (valid memory; those results are never stored).
-__device__ __forceinline__ void bf_issue(const uint16_t *__restrict__ hi, const uint16_t *__restrict__ lo,
-                                         int64_t npad, int64_t p, int64_t j0, int64_t k0, int64_t i0,
-                                         bool diag, unsigned char *stage)
+// Issue the copies of one stage.  A diagonal tile copies its one panel only.
+// Row blocks past the last load that one (those results are never stored).
+__device__ __forceinline__ void bf_issue(const uint16_t *__restrict__ split, int ks, int64_t rbs, int64_t rj,
+                                         int64_t rk, int st, bool diag, unsigned char *stage)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int npan = diag ? 2 : 4;
-    // 16 groups of 16 rows per panel; one 1 KB wave instruction per group
-    for (int blk = wv; blk < npan * 16; blk += 8) {
-        const int pnl = blk >> 4, grp = blk & 15;
-        const int m = grp * 16 + (lane >> 2);
-        const int c = (lane & 3) ^ bf_swz(m);
-        int64_t v = ((pnl < 2) ? j0 : k0) + m;
-        v = v < p ? v : p - 1;
-        const uint16_t *src = ((pnl & 1) ? lo : hi) + v * npad + i0 + c * 8;
-        __builtin_amdgcn_global_load_lds(
-            src, (__attribute__((address_space(3))) void *)(stage + pnl * kBfPanel + grp * 1024), 16, 0, 0);
-    }
+    // wave wv copies row blocks wv and wv + 8 of each panel, hi and lo
+    const int npan = diag ? 1 : 2;
+    for (int pnl = 0; pnl < npan; ++pnl)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int g = wv + 8 * h;
+            int64_t rb = (pnl ? rk : rj) + g;
+            rb = rb < rbs ? rb : rbs - 1;
+            const uint16_t *src = split + (rb * ks + st) * 1024 + lane * 8;
+#pragma unroll
+            for (int part = 0; part < 2; ++part)
+                __builtin_amdgcn_global_load_lds(
+                    src + part * 512,
+                    (__attribute__((address_space(3))) void *)(stage + pnl * kBfPanel + g * 2048 + part * 1024), 16,
+                    0, 0);
+        }
 }
 
 // One 256 x 256 tile (bj, bk) of one problem's S, by the whole block.
-__device__ __forceinline__ void bf_tile_run(const uint16_t *__restrict__ hi, const uint16_t *__restrict__ lo,
-                                            int64_t npad, int64_t p, float *__restrict__ S, float invn, float thr,
-                                            int *__restrict__ scnt, int *__restrict__ sidx, int bj, int bk,
-                                            unsigned char *bf_lds)
+template <bool NT>
+__device__ __forceinline__ void bf_tile256(const uint16_t *__restrict__ split, int64_t npad, int64_t p,
+                                           float *__restrict__ S, float invn, float thr, int *__restrict__ scnt,
+                                           int *__restrict__ sidx, int bj, int bk, unsigned char *bf_lds)
 {
     BfScreen &scr = *reinterpret_cast<BfScreen *>(bf_lds + 2 * kBfStage);
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int wm = w & 3, wn = w >> 2;
-    const int nst = (int)(npad / kBfKC);
-    const bool vec_ok = (p & 3) == 0;  // rows of S 16-byte aligned
-    {
-        const int64_t j0 = (int64_t)bj * kBfTile, k0 = (int64_t)bk * kBfTile;
-        const bool diag = bj == bk;
-        const int pk = diag ? 0 : 2;  // panels the column block reads
-        f4 acc[4][8];
+    const int ks = (int)(npad / kBfKC);  // even
+    const int64_t rbs = (p + 15) / 16;
+    const int64_t j0 = (int64_t)bj * kBfTile, k0 = (int64_t)bk * kBfTile;
+    const bool diag = bj == bk;
+    f4 acc[4][8];
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int b = 0; b < 8; ++b) acc[a][b] = f4{0, 0, 0, 0};
-        __syncthreads();  // the previous tile's epilogue and flush are done with the LDS
-        int nscr = 0;     // this wave's screen entries (wave-uniform)
-        bf_issue(hi, lo, npad, p, j0, k0, 0, diag, bf_lds);
-        for (int st = 0; st < nst; ++st) {
-            __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of stage st have landed
-            __syncthreads();                // ... every wave's; stage st - 1 is consumed
-            if (st + 1 < nst)
-                bf_issue(hi, lo, npad, p, j0, k0, (int64_t)(st + 1) * kBfKC, diag,
-                         bf_lds + ((st + 1) & 1) * kBfStage);
-            const unsigned char *sb = bf_lds + (st & 1) * kBfStage;
-            const int c = lane >> 4;
-            bf8 ha[4], la[4], hb[8], lb[8];
+        for (int b = 0; b < 8; ++b) acc[a][b] = f4{0, 0, 0, 0};
+    const unsigned char *const la0 = bf_lds + wm * 8192 + lane * 16;
+    const unsigned char *const lb0 = bf_lds + (diag ? 0 : kBfPanel) + wn * 16384 + lane * 16;
+    bf8 ha[2][4], la[2][4], hb[4], lb[4];
+    auto read_a = [&](int buf) {
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int m = 64 * wm + 16 * a + (lane & 15);
-                const int off = m * 64 + ((c ^ bf_swz(m)) << 4);
-                ha[a] = *reinterpret_cast<const bf8 *>(sb + off);
-                la[a] = *reinterpret_cast<const bf8 *>(sb + kBfPanel + off);
-            }
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int m = 128 * wn + 16 * b + (lane & 15);
-                const int off = m * 64 + ((c ^ bf_swz(m)) << 4);
-                hb[b] = *reinterpret_cast<const bf8 *>(sb + pk * kBfPanel + off);
-                lb[b] = *reinterpret_cast<const bf8 *>(sb + (pk + 1) * kBfPanel + off);
-            }
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(la[a], hb[b], acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha[a], lb[b], acc[a][b], 0, 0, 0);
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha[a], hb[b], acc[a][b], 0, 0, 0);
-                }
+        for (int a = 0; a < 4; ++a) {
+            ha[buf][a] = *reinterpret_cast<const bf8 *>(la0 + buf * kBfStage + a * 2048);
+            la[buf][a] = *reinterpret_cast<const bf8 *>(la0 + buf * kBfStage + a * 2048 + 1024);
         }
-        // epilogue, straight from the accumulators: lane l holds rows
-        // jb .. jb + 3 (jb = 4 (l / 16) within the 16 x 16 block) of column
-        // kk = l % 16.  Direct: 16 lanes store 64 consecutive bytes of a row
-        // of S; mirrored: the lane's four rows are four consecutive columns
-        // of row kk, one 16-byte store.  A diagonal tile stores its upper
-        // triangle both ways, so S is symmetric bit for bit.
-        const int g4 = 4 * (lane >> 4), c16 = lane & 15;
+    };
+    auto read_b = [&](int buf, int b, int slot) {
+        hb[slot] = *reinterpret_cast<const bf8 *>(lb0 + buf * kBfStage + b * 2048);
+        lb[slot] = *reinterpret_cast<const bf8 *>(lb0 + buf * kBfStage + b * 2048 + 1024);
+    };
+    auto mul = [&](int buf, int b, int slot) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < 4; ++a) acc[a][b] = bf_mma(ha[buf][a], la[buf][a], hb[slot], lb[slot], acc[a][b]);
+    };
+    __syncthreads();  // the previous tile's flush is done with the LDS
+    bf_issue(split, ks, rbs, j0 / 16, k0 / 16, 0, diag, bf_lds);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    bf_issue(split, ks, rbs, j0 / 16, k0 / 16, 1, diag, bf_lds + kBfStage);
+    read_a(0);
+    read_b(0, 0, 0);
+    for (int s0 = 0; s0 < ks; s0 += 2) {
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int64_t kk = k0 + 128 * wn + 16 * b + c16;
-                const int64_t jb = j0 + 64 * wm + 16 * a + g4;
-                float v[4];
+        for (int cur = 0; cur < 2; ++cur) {
+            // blocks b = 0 .. 5 in slots 0 and 1, 6 and 7 in slots 2 and 3
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = jb + r == kk ? 1.0f : acc[a][b][r] * invn;
-                // screen: a pair above the threshold is a candidate of both
-                // columns (every lane takes part in the ballots)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool mine = jb + r < p && kk < p && (!diag || jb + r < kk);
-                    screen_pair_wave(scr, w, nscr, scnt, sidx, thr, jb + r, kk, mine ? v[r] : 0.0f);
-                }
-                if (kk >= p) continue;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (jb + r < p && (!diag || jb + r <= kk)) S[(jb + r) * p + kk] = v[r];
-                if (vec_ok && jb + 3 < p && (!diag || kk > jb + 3)) {
-                    *reinterpret_cast<f4 *>(&S[kk * p + jb]) = f4{v[0], v[1], v[2], v[3]};
+            for (int b = 0; b < 6; ++b) {
+                if (b < 5) {
+                    read_b(cur, b + 1, (b + 1) & 1);
                 } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (jb + r < p && (!diag || kk > jb + r)) S[kk * p + jb + r] = v[r];
+                    read_b(cur, 6, 2);
+                    read_b(cur, 7, 3);
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                mul(cur, b, b & 1);
+                __builtin_amdgcn_sched_barrier(0);
             }
-        if (lane == 0) scr.n[w] = nscr;
-        __syncthreads();
-        screen_flush_waves(scr, scnt, sidx);
+            if (s0 + cur + 1 < ks) {
+                // this wave's reads of the stage are done and its copies of
+                // the next have landed; past the barrier every wave's are
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                if (s0 + cur + 2 < ks)
+                    bf_issue(split, ks, rbs, j0 / 16, k0 / 16, s0 + cur + 2, diag, bf_lds + cur * kBfStage);
+                read_a(cur ^ 1);
+                read_b(cur ^ 1, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            mul(cur, 6, 2);
+            mul(cur, 7, 3);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
+    const int nscr = bf_store<4, 8, NT>(acc, S, p, j0 + 64 * wm, k0 + 128 * wn, diag, invn, thr, scnt, sidx, scr, w);
+    if (lane == 0) scr.n[w] = nscr;
+    __syncthreads();
+    screen_flush_waves(scr, scnt, sidx);
 }
 
-__global__ __launch_bounds__(512) void k_syrk_bf16x3(const uint16_t *__restrict__ hi,
-                                                     const uint16_t *__restrict__ lo,
-                                                     int64_t npad, int64_t p,
-                                                     float *__restrict__ S, int Tt, float invn,
-                                                     float thr, int *__restrict__ scnt,
-                                                     int *__restrict__ sidx)
+template <bool NT>
+__global__ __launch_bounds__(512) void k_syrk_bf16x3_256(const uint16_t *__restrict__ split, int64_t npad, int64_t p,
+                                                         float *__restrict__ S, int Tt, float invn, float thr,
+                                                         int *__restrict__ scnt, int *__restrict__ sidx)
 {
     extern __shared__ __align__(16) unsigned char bf_lds[];
-    const int ntiles = Tt * (Tt + 1) / 2;
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int64_t ntiles = (int64_t)Tt * (Tt + 1) / 2;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         int bj, bk;
-        bf_tile(t, Tt, &bj, &bk);
-        bf_tile_run(hi, lo, npad, p, S, invn, thr, scnt, sidx, bj, bk, bf_lds);
+        tri_tile(Tt, t, &bj, &bk);
+        bf_tile256<NT>(split, npad, p, S, invn, thr, scnt, sidx, bj, bk, bf_lds);
     }
 }
 
-// The tiles of many problems in one launch: tile g is tile g - off[d] of
-// problem d (its own upper-triangle order).
-__global__ __launch_bounds__(512) void k_syrk_bf16x3_grouped(const SyrkJob *__restrict__ tab,
-                                                             const int64_t *__restrict__ off, int nd)
+__global__ __launch_bounds__(512) void k_syrk_bf16x3_256_grouped(const SyrkJob *__restrict__ tab,
+                                                                 const int64_t *__restrict__ off, int nd)
 {
     extern __shared__ __align__(16) unsigned char bf_lds[];
     const int64_t total = off[nd];
@@ -790,21 +934,26 @@ __global__ __launch_bounds__(512) void k_syrk_bf16x3_grouped(const SyrkJob *__re
         const int d = group_of(off, nd, g);
         const SyrkJob &J = tab[d];
         int bj, bk;
-        bf_tile((int)(g - off[d]), J.Tt, &bj, &bk);
-        bf_tile_run(J.hi, J.lo, J.npad, J.p, J.S, J.invn, J.thr, J.scnt, J.sidx, bj, bk, bf_lds);
+        tri_tile(J.Tt, g - off[d], &bj, &bk);
+        bf_tile256<false>(J.split, J.npad, J.p, J.S, J.invn, J.thr, J.scnt, J.sidx, bj, bk, bf_lds);
     }
 }
 
-SyrkJob syrk_job_bf16x3(const uint16_t *hi, const uint16_t *lo, int64_t n, int64_t npad, int64_t p, float *S,
-                        const Screen &sc, int64_t *tiles)
+// Tile edge from the number of 256 x 256 tiles of the launch: both kernels
+// take 84 us at n = 1000, p = 4000 (136 of them); with 120 the 64 x 64 tiles
+// take 43 us against 49 (n = 400, p = 3700), with 210 they take 73 against
+// 54 (n = 400, p = 5000).
+int syrk_bf16x3_edge(int64_t tiles256) { return tiles256 >= 144 ? kBfTile : kBfSmall; }
+
+SyrkJob syrk_job_bf16x3(const uint16_t *split, int64_t n, int64_t npad, int64_t p, float *S, const Screen &sc,
+                        int edge, int64_t *tiles)
 {
     SyrkJob j{};
-    j.hi = hi;
-    j.lo = lo;
+    j.split = split;
     j.npad = npad;
     j.p = p;
     j.S = S;
-    j.Tt = (int)((p + kBfTile - 1) / kBfTile);
+    j.Tt = (int)((p + edge - 1) / edge);
     j.invn = (float)(1.0 / (double)n);
     j.thr = sc.thr32;
     j.scnt = sc.cnt;
@@ -813,22 +962,41 @@ SyrkJob syrk_job_bf16x3(const uint16_t *hi, const uint16_t *lo, int64_t n, int64
     return j;
 }
 
-void launch_syrk_bf16x3_grouped(const SyrkJob *tab, const int64_t *tile_off, int nd, int64_t tiles, hipStream_t s)
+// 256 x 256 tiles: one block per CU (LDS and registers), at most one per tile
+static unsigned bf_grid256(int64_t tiles) { return (unsigned)(tiles < 256 ? tiles : 256); }
+
+void launch_syrk_bf16x3_grouped(const SyrkJob *tab, const int64_t *tile_off, int nd, int64_t tiles, int edge,
+                                hipStream_t s)
 {
     if (tiles <= 0) return;
-    const int64_t grid = tiles < 256 ? tiles : 256;
-    hipLaunchKernelGGL(k_syrk_bf16x3_grouped, dim3((unsigned)grid), dim3(512), kBfLds, s, tab, tile_off, nd);
+    if (edge == kBfTile)
+        hipLaunchKernelGGL(k_syrk_bf16x3_256_grouped, dim3(bf_grid256(tiles)), dim3(512), kBfLds, s, tab, tile_off,
+                           nd);
+    else
+        hipLaunchKernelGGL(k_syrk_bf16x3_64_grouped, dim3((unsigned)tiles), dim3(256), 0, s, tab, tile_off, nd);
 }
 
-void launch_syrk_bf16x3(const uint16_t *hi, const uint16_t *lo, int64_t n, int64_t npad,
-                        int64_t p, float *S, const Screen &sc, hipStream_t s)
+void launch_syrk_bf16x3(const uint16_t *split, int64_t n, int64_t npad, int64_t p, float *S, const Screen &sc,
+                        hipStream_t s)
 {
-    int Tt = (int)((p + kBfTile - 1) / kBfTile);
-    int64_t ntiles = (int64_t)Tt * (Tt + 1) / 2;
-    // one block per CU (LDS and registers), at most one per tile
-    int64_t grid = ntiles < 256 ? ntiles : 256;
-    hipLaunchKernelGGL(k_syrk_bf16x3, dim3((unsigned)grid), dim3(512), kBfLds, s, hi, lo, npad, p, S,
-                       Tt, (float)(1.0 / (double)n), sc.thr32, sc.cnt, sc.idx);
+    const int64_t t256 = (p + kBfTile - 1) / kBfTile;
+    const int edge = syrk_bf16x3_edge(t256 * (t256 + 1) / 2);
+    const int Tt = (int)((p + edge - 1) / edge);
+    const int64_t tiles = (int64_t)Tt * (Tt + 1) / 2;
+    const float invn = (float)(1.0 / (double)n);
+    // an S larger than the 256 MB memory-side cache is stored past it (with
+    // ordinary stores p = 20000 takes 2% longer, and the pass that reads S
+    // next 5%; a smaller S is better left in the cache)
+    const bool nt = 4 * p * p > (int64_t)256 << 20;
+    if (edge == kBfTile && nt)
+        hipLaunchKernelGGL(k_syrk_bf16x3_256<true>, dim3(bf_grid256(tiles)), dim3(512), kBfLds, s, split, npad, p, S,
+                           Tt, invn, sc.thr32, sc.cnt, sc.idx);
+    else if (edge == kBfTile)
+        hipLaunchKernelGGL(k_syrk_bf16x3_256<false>, dim3(bf_grid256(tiles)), dim3(512), kBfLds, s, split, npad, p, S,
+                           Tt, invn, sc.thr32, sc.cnt, sc.idx);
+    else
+        hipLaunchKernelGGL(k_syrk_bf16x3_64, dim3((unsigned)tiles), dim3(256), 0, s, split, npad, p, S, Tt, invn,
+                           sc.thr32, sc.cnt, sc.idx);
 }
 
 } // namespace spmesl
