@@ -134,7 +134,8 @@ typedef struct {
 #define SPMESL_FLAG_TIMING 1
 /* Enqueue the kernels one by one instead of replaying the context's cached
  * HIP graph of the call (the default for calls that repeat the pointers,
- * sizes and options of the previous call; timed calls are always eager). */
+ * sizes and options of one of the last calls; timed calls are always
+ * eager). */
 #define SPMESL_FLAG_EAGER 2
 /* Mixed form: the double polish proves every column by a full pass over S
  * (every j with |g_j| within the float error bound of lambda joins the
@@ -294,7 +295,7 @@ typedef struct {
 int spmesl_set_tuning(spmesl_ctx *ctx, const spmesl_tuning *t);
 int spmesl_get_tuning(const spmesl_ctx *ctx, spmesl_tuning *t);
 
-/* Autotuner: times solves of this problem (graph replays, the fastest of
+/* Autotuner: times solves of this problem (kernel by kernel, the fastest of
  * three runs of `reps` per candidate, HIP events on the context's stream;
  * a candidate must be at least 1% faster to be kept) over the candidate values
  * of each field in turn (coordinate search from the current shapes: screen

@@ -250,7 +250,7 @@ void launch_syrk_mfma_grouped(const SyrkJobT<T> *tab, const int64_t *tile_off, i
                               hipStream_t s);
 // Tile edge of the mixed form's kernel (256 or 64) from the number of
 // 256 x 256 tiles of the launch.
-int syrk_bf16x3_edge(int64_t tiles256);
+int syrk_bf16x3_edge(int64_t tiles256, bool grouped);
 SyrkJob syrk_job_bf16x3(const uint16_t *split, int64_t n, int64_t npad, int64_t p, float *S, const Screen &sc,
                         int edge, int64_t *tiles);
 void launch_syrk_bf16x3_grouped(const SyrkJob *tab, const int64_t *tile_off, int nd, int64_t tiles, int edge,

@@ -942,8 +942,13 @@ __global__ __launch_bounds__(512) void k_syrk_bf16x3_256_grouped(const SyrkJob *
 // Tile edge from the number of 256 x 256 tiles of the launch: both kernels
 // take 84 us at n = 1000, p = 4000 (136 of them); with 120 the 64 x 64 tiles
 // take 43 us against 49 (n = 400, p = 3700), with 210 they take 73 against
-// 54 (n = 400, p = 5000).
-int syrk_bf16x3_edge(int64_t tiles256) { return tiles256 >= 144 ? kBfTile : kBfSmall; }
+// 54 (n = 400, p = 5000).  A batch's tiles are of many sizes (most of a small
+// problem's large tile is padding, and the launch ends on the longest), so
+// its large tiles have to come to two rounds of the chip.
+int syrk_bf16x3_edge(int64_t tiles256, bool grouped)
+{
+    return tiles256 >= (grouped ? 512 : 144) ? kBfTile : kBfSmall;
+}
 
 SyrkJob syrk_job_bf16x3(const uint16_t *split, int64_t n, int64_t npad, int64_t p, float *S, const Screen &sc,
                         int edge, int64_t *tiles)
@@ -980,7 +985,7 @@ void launch_syrk_bf16x3(const uint16_t *split, int64_t n, int64_t npad, int64_t 
                         hipStream_t s)
 {
     const int64_t t256 = (p + kBfTile - 1) / kBfTile;
-    const int edge = syrk_bf16x3_edge(t256 * (t256 + 1) / 2);
+    const int edge = syrk_bf16x3_edge(t256 * (t256 + 1) / 2, false);
     const int Tt = (int)((p + edge - 1) / edge);
     const int64_t tiles = (int64_t)Tt * (Tt + 1) / 2;
     const float invn = (float)(1.0 / (double)n);
