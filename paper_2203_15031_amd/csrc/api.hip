@@ -355,7 +355,7 @@ struct spmesl_ctx {
         std::vector<unsigned char> key;
         hipGraphExec_t exec = nullptr;
     };
-    static constexpr size_t kMaxGraphs = 16;
+    static constexpr size_t kMaxGraphs = 64;
     std::vector<CachedGraph> graphs;
     // the last distinct calls that ran kernel by kernel, most recent first
     static constexpr size_t kMaxSeen = 4;
@@ -1419,16 +1419,18 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_op
     BatchGrids gr;
     for (int i = 0; i < count; ++i) gr.rj = std::min(gr.rj, kkt_rows_for<T>(plans[(size_t)i].p, 0, tu));
     {
-        // the large tiles by the same rules as one problem's, on the batch's
-        // total of them
-        const int64_t big = sizeof(T) == 8 ? 128 : 256;
-        int64_t nbig = 0;
-        for (int i = 0; i < count; ++i) {
-            const int64_t e = (plans[(size_t)i].p + big - 1) / big;
-            nbig += e * (e + 1) / 2;
-        }
-        if (sizeof(T) == 8) gr.syrk_edge = nbig >= 256 ? 128 : 64;
-        else if (plans[0].prec == SPMESL_MIXED) gr.syrk_edge = syrk_bf16x3_edge(nbig, true);
+        // the tile edge by the same rules as one problem's, on the batch's
+        // totals of tiles
+        auto total = [&](int64_t edge) {
+            int64_t t = 0;
+            for (int i = 0; i < count; ++i) {
+                const int64_t e = (plans[(size_t)i].p + edge - 1) / edge;
+                t += e * (e + 1) / 2;
+            }
+            return t;
+        };
+        gr.syrk_edge = plans[0].prec == SPMESL_MIXED ? syrk_bf16x3_edge(total(256), true)
+                                                     : syrk_edge(total(64), total(128), sizeof(T) == 8);
     }
     auto *first = (ColArgs<T> *)(h + t.first);
     auto *resume = (ColArgs<T> *)(h + t.resume);

@@ -241,8 +241,8 @@ struct SyrkJobT {
     int64_t pv;
     int *scnt, *sidx;
 };
-// Tiles of `edge` (the double form: 128 or 64, see syrk_f64_edge; float: 64).
-int syrk_f64_edge(int64_t p);
+// Tile edge (32, 64 or 128) of the double and float forms' kernels.
+int syrk_edge(int64_t tiles64, int64_t tiles128, bool dbl);
 template <typename T>
 SyrkJobT<T> syrk_job_mfma(const T *Xs, int64_t n, int64_t p, T *S, const Screen &sc, int edge, int64_t *tiles);
 template <typename T>

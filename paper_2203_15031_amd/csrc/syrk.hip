@@ -1,7 +1,7 @@
 // syrk.hip -- the sample covariance S = Xs^T Xs / n on the matrix cores.
 //
 // S is the only dense contraction of the method (n p^2 multiply-adds).  Only
-// the upper triangle of 64x64 (or 128x128) tiles is computed; each tile is
+// the upper triangle of square tiles is computed; each tile is
 // written twice, once as is and once transposed, so S is stored full and
 // every row of S is a contiguous read for the solver.  The diagonal is set
 // to exactly 1 (s_jj = 1 for standardised columns, Section 2.2), which the
@@ -12,7 +12,7 @@
 //   * float : v_mfma_f32_16x16x4f32, same layout;
 //   * mixed : two-term bfloat16 split x = hi + lo of float(x), products
 //             hi*hi + hi*lo + lo*hi accumulated in float by
-//             v_mfma_f32_16x16x32_bf16 from variable-major hi/lo panels.
+//             v_mfma_f32_16x16x32_bf16 (the split in operand order).
 //
 // Operand layout of the 16x16xK MFMAs used here (wave64): lane l supplies
 // row l%16 of A and column l%16 of B, at k-block l/16.  Accumulator element r
@@ -44,65 +44,11 @@ template <typename T> __device__ __forceinline__ int acc_row(int lane, int r);
 template <> __device__ __forceinline__ int acc_row<double>(int lane, int r) { return 4 * r + (lane >> 4); }
 template <> __device__ __forceinline__ int acc_row<float>(int lane, int r) { return 4 * (lane >> 4) + r; }
 
-// The screen (see Screen): entry s_jk = v makes j a candidate of column k.
-// Candidates of a tile are collected in LDS (a short list; an LDS atomic
-// returns quickly) and flushed with one round of global atomics per tile, so
-// no wave waits on a global atomic inside the store loops.
-template <int N>
-struct ScreenLds {
-    static constexpr int kCap = N;  // candidates a tile collects before storing directly
-    int n;
-    int jk[2 * N];
-};
-
-// Entry s_jk = v makes j a candidate of column k when |v| > thr and j < pv
-// (pv: the candidate variables; p for SPMESL).
-template <typename L, typename T>
-__device__ __forceinline__ void screen_entry(L &lst, int *cnt, int *idx, T thr, int64_t pv, int64_t j, int64_t k,
-                                             T v)
-{
-    const bool hit = cnt && j != k && j < pv && (v < T(0) ? -v : v) > thr;
-    if (!__ballot(hit)) return;  // the common case: one wave-uniform branch
-    if (hit) {
-        const int q = atomicAdd(&lst.n, 1);
-        if (q < L::kCap) {
-            lst.jk[2 * q] = (int)j;
-            lst.jk[2 * q + 1] = (int)k;
-        } else {
-            const int pos = atomicAdd(&cnt[k], 1);
-            if (pos < kPendMax) idx[k * kPendMax + pos] = (int)j;
-        }
-    }
-}
-
-// Entry s_jk = s_kj = v of a symmetric pair (j != k) makes j a candidate of
-// column k and k one of column j; v = 0 records nothing.  The wave's hits
-// take their list slots with one LDS atomic.
-template <typename L, typename T>
-__device__ __forceinline__ void screen_pair(L &lst, int *cnt, int *idx, T thr, int64_t j, int64_t k, T v)
-{
-    const bool hit = cnt && j != k && (v < T(0) ? -v : v) > thr;
-    const unsigned long long mask = __ballot(hit);
-    if (!mask) return;  // the common case: one wave-uniform branch
-    const int lead = __builtin_ffsll((long long)mask) - 1;
-    int base = 0;
-    if (lane_id() == lead) base = atomicAdd(&lst.n, 2 * __popcll(mask));
-    base = __shfl(base, lead);
-    if (!hit) return;
-    const int q = base + 2 * lanes_below(mask);
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-        const int a = (int)(d ? k : j), b = (int)(d ? j : k);  // a joins column b
-        if (q + d < L::kCap) {
-            lst.jk[2 * (q + d)] = a;
-            lst.jk[2 * (q + d) + 1] = b;
-        } else {
-            const int pos = atomicAdd(&cnt[b], 1);
-            if (pos < kPendMax) idx[(int64_t)b * kPendMax + pos] = a;
-        }
-    }
-}
-
+// The screen (see Screen): entry s_jk = s_kj = v of a symmetric pair (j != k)
+// makes j a candidate of column k and k one of column j (those below pv);
+// v = 0 records nothing.  Candidates of a tile are collected in LDS and
+// flushed with one round of global atomics per tile, so no wave waits on a
+// global atomic inside the store loops.
 // Per-wave candidate lists (no atomics): wave w appends to its own segment
 // and keeps the count in a wave-uniform register.
 template <int NW, int N>
@@ -112,8 +58,9 @@ struct ScreenWaves {
     int jk[NW][2 * N];
 };
 
-template <typename L, typename T>
-__device__ __forceinline__ void screen_pair_wave(L &lst, int wv, int &count, int *cnt, int *idx, T thr,
+// PV: only variables below pv are candidates (else every variable is).
+template <bool PV, typename L, typename T>
+__device__ __forceinline__ void screen_pair_wave(L &lst, int wv, int &count, int *cnt, int *idx, T thr, int64_t pv,
                                                  int64_t j, int64_t k, T v)
 {
     const bool hit = cnt && j != k && (v < T(0) ? -v : v) > thr;
@@ -124,11 +71,13 @@ __device__ __forceinline__ void screen_pair_wave(L &lst, int wv, int &count, int
     if (!hit) return;
 #pragma unroll
     for (int d = 0; d < 2; ++d) {
-        const int a = (int)(d ? k : j), b = (int)(d ? j : k);  // a joins column b
+        int a = (int)(d ? k : j);        // a joins column b
+        const int b = (int)(d ? j : k);
+        if (PV && a >= pv) a = -1;       // no candidate: an empty slot
         if (q + d < L::kCap) {
             lst.jk[wv][2 * (q + d)] = a;
             lst.jk[wv][2 * (q + d) + 1] = b;
-        } else {
+        } else if (!PV || a >= 0) {
             const int pos = atomicAdd(&cnt[b], 1);
             if (pos < kPendMax) idx[(int64_t)b * kPendMax + pos] = a;
         }
@@ -150,7 +99,7 @@ __device__ __forceinline__ void screen_flush_waves(ScreenWaves<NW, N> &lst, int 
                 jj[u] = 0;
                 if (q < m) {
                     jj[u] = lst.jk[w][2 * q];
-                    pos[u] = atomicAdd(&cnt[lst.jk[w][2 * q + 1]], 1);
+                    if (jj[u] >= 0) pos[u] = atomicAdd(&cnt[lst.jk[w][2 * q + 1]], 1);
                 }
             }
 #pragma unroll
@@ -158,35 +107,6 @@ __device__ __forceinline__ void screen_flush_waves(ScreenWaves<NW, N> &lst, int 
                 const int q = q0 + u * (int)blockDim.x;
                 if (q < m && pos[u] < kPendMax) idx[(int64_t)lst.jk[w][2 * q + 1] * kPendMax + pos[u]] = jj[u];
             }
-        }
-    }
-}
-
-// After the tile's entries are collected (and a barrier): store them.  The
-// persistent kernel calls this for a tile while the next tile's first stage
-// is being copied, so the atomics' round trip overlaps the copy.
-template <typename L>
-__device__ __forceinline__ void screen_flush(L &lst, int *cnt, int *idx)
-{
-    if (!cnt) return;
-    const int m = lst.n < L::kCap ? lst.n : L::kCap;
-    // up to eight independent atomics per thread in flight, then the stores
-    for (int q0 = threadIdx.x; q0 < m; q0 += 8 * (int)blockDim.x) {
-        int jj[8], pos[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int q = q0 + u * (int)blockDim.x;
-            pos[u] = kPendMax;
-            jj[u] = 0;
-            if (q < m) {
-                jj[u] = lst.jk[2 * q];
-                pos[u] = atomicAdd(&cnt[lst.jk[2 * q + 1]], 1);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int q = q0 + u * (int)blockDim.x;
-            if (q < m && pos[u] < kPendMax) idx[(int64_t)lst.jk[2 * q + 1] * kPendMax + pos[u]] = jj[u];
         }
     }
 }
@@ -238,322 +158,212 @@ __device__ __forceinline__ void tile_of_block(int T, int *bj, int *bk)
     tri_tile(T, xcd_order(gridDim.x, blockIdx.x), bj, bk);
 }
 
-constexpr int kSyrkKC = 32;
-
-template <typename T>
-struct SyrkMfmaSm {
-    union {
-        struct {
-            T a[kSyrkKC][64];
-            T b[kSyrkKC][64];
-        } in;
-        T out[64][65];
-    };
-};
-
-// One 64 x 64 tile (bj, bk) of S by the block; scr: the screen's list (a
-// 64 x 64 tile: about 6 per row at the workloads here).
-template <typename T>
-__device__ __forceinline__ void syrk_mfma_tile(const T *__restrict__ Xs, int64_t n, int64_t p, T *__restrict__ S,
-                                               int bj, int bk, T invn, T thr, int64_t pv, int *__restrict__ scnt,
-                                               int *__restrict__ sidx, SyrkMfmaSm<T> &sm, ScreenLds<512> &scr)
+template <bool NT, typename V> __device__ __forceinline__ void store_s(V *at, V v)
 {
-    typedef typename Acc<T>::type AccT;
-    const int64_t j0 = (int64_t)bj * 64, k0 = (int64_t)bk * 64;
-    if (threadIdx.x == 0) scr.n = 0;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wm = w & 1, wn = w >> 1;
-    AccT acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = AccT{0, 0, 0, 0};
+    if constexpr (NT) __builtin_nontemporal_store(v, at);
+    else *at = v;
+}
 
-    // loader mapping: rows lr and lr + 16 of the chunk, 4 consecutive columns
-    const int lr = tid >> 4, lc = (tid & 15) * 4;
-    constexpr int NL = kSyrkKC / 16;
-    T ra[NL][4], rb[NL][4];
-    auto fetch = [&](int64_t i0) {
+// A wave's NA x NB accumulator blocks (from variable j0 / k0 of S) to S and
+// the screen (PV: candidates j < pv), straight from the accumulators: element
+// r of lane l is row acc_row(l, r), column l % 16 of its 16 x 16 block.
+// Direct: 16 lanes store consecutive entries of a row of S; mirrored: in the
+// float layout the lane's four rows are four consecutive columns of row kk,
+// one 16-byte store.  A diagonal tile stores its upper triangle both ways, so
+// S is symmetric bit for bit.  NT: nontemporal stores.  Returns the wave's
+// count of screen entries.
+template <typename T, int NA, int NB, bool NT, bool PV, typename SCR>
+__device__ __forceinline__ int store_tile(const typename Acc<T>::type (&acc)[NA][NB], T *__restrict__ S, int64_t p,
+                                          int64_t j0, int64_t k0, bool diag, T invn, T thr, int64_t pv,
+                                          int *__restrict__ scnt, int *__restrict__ sidx, SCR &scr, int w)
+{
+    const int lane = threadIdx.x & 63;
+    const int c16 = lane & 15;
+    const bool vec_ok = sizeof(T) == 4 && (p & 3) == 0;  // rows of S 16-byte aligned
+    const int jl = acc_row<T>(lane, 0);
+    constexpr int JS = sizeof(T) == 4 ? 1 : 4;           // row step per element
+    int nscr = 0;
 #pragma unroll
-        for (int h = 0; h < NL; ++h) {
-            int64_t i = i0 + lr + 16 * h;
+    for (int a = 0; a < NA; ++a)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                int64_t ja = j0 + lc + e, kb = k0 + lc + e;
-                ra[h][e] = (i < n && ja < p) ? Xs[i * p + ja] : T(0);
-                rb[h][e] = (i < n && kb < p) ? Xs[i * p + kb] : T(0);
+        for (int b = 0; b < NB; ++b) {
+            const int64_t kk = k0 + 16 * b + c16;
+            const int64_t jb = j0 + 16 * a + jl;
+            T v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = jb + JS * r == kk ? T(1) : acc[a][b][r] * invn;
+            // screen: a pair above the threshold is a candidate of both
+            // columns (every lane takes part in the ballots)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool mine = jb + JS * r < p && kk < p && (!diag || jb + JS * r < kk);
+                screen_pair_wave<PV>(scr, w, nscr, scnt, sidx, thr, pv, jb + JS * r, kk, mine ? v[r] : T(0));
             }
-        }
-    };
-    fetch(0);
-    for (int64_t i0 = 0; i0 < n; i0 += kSyrkKC) {
-#pragma unroll
-        for (int h = 0; h < NL; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sm.in.a[lr + 16 * h][lc + e] = ra[h][e];
-                sm.in.b[lr + 16 * h][lc + e] = rb[h][e];
-            }
-        __syncthreads();
-        if (i0 + kSyrkKC < n) fetch(i0 + kSyrkKC);  // in flight during the MFMAs below
-#pragma unroll
-        for (int kk = 0; kk < kSyrkKC; kk += 4) {
-            T av[2], bv[2];
-#pragma unroll
-            for (int a = 0; a < 2; ++a) av[a] = sm.in.a[kk + (lane >> 4)][32 * wm + 16 * a + (lane & 15)];
-#pragma unroll
-            for (int b = 0; b < 2; ++b) bv[b] = sm.in.b[kk + (lane >> 4)][32 * wn + 16 * b + (lane & 15)];
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[a][b] = mfma16x16x4(av[a], bv[b], acc[a][b]);
-        }
-        __syncthreads();
-    }
-    // stage the tile (scaled by 1/n) for coalesced direct and mirrored writes
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
+            if (kk >= p) continue;
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                sm.out[32 * wm + 16 * a + acc_row<T>(lane, r)][32 * wn + 16 * b + (lane & 15)] =
-                    acc[a][b][r] * invn;
-    __syncthreads();
-    // a diagonal tile takes its upper triangle for both halves, so S is
-    // symmetric bit for bit whatever the accumulation order
-    const bool diag = bj == bk;
-    for (int e = tid; e < 64 * 64; e += 256) {
-        int rr = e >> 6, cc = e & 63;
-        int64_t j = j0 + rr, k = k0 + cc;
-        if (j < p && k < p) {
-            const T v = (j == k) ? T(1) : ((diag && rr > cc) ? sm.out[cc][rr] : sm.out[rr][cc]);
-            S[j * p + k] = v;
-            screen_entry(scr, scnt, sidx, thr, pv, j, k, v);
-        }
-    }
-    if (bj != bk) {
-        for (int e = tid; e < 64 * 64; e += 256) {
-            int rr = e >> 6, cc = e & 63;  // row of the mirrored tile = k index
-            int64_t k = k0 + rr, j = j0 + cc;
-            if (j < p && k < p) {
-                const T v = sm.out[cc][rr];
-                S[k * p + j] = v;
-                screen_entry(scr, scnt, sidx, thr, pv, k, j, v);
+                if (jb + JS * r < p && (!diag || jb + JS * r <= kk)) store_s<NT>(&S[(jb + JS * r) * p + kk], v[r]);
+            if (vec_ok && jb + 3 < p && (!diag || kk > jb + 3)) {
+                if constexpr (sizeof(T) == 4)
+                    store_s<NT>(reinterpret_cast<f4 *>(&S[kk * p + jb]), f4{v[0], v[1], v[2], v[3]});
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (jb + JS * r < p && (!diag || kk > jb + JS * r)) store_s<NT>(&S[kk * p + jb + JS * r], v[r]);
             }
         }
-    }
-    __syncthreads();
-    screen_flush(scr, scnt, sidx);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_syrk_mfma(const T *__restrict__ Xs, int64_t n, int64_t p,
-                                                   T *__restrict__ S, int Tt, T invn, T thr, int64_t pv,
-                                                   int *__restrict__ scnt, int *__restrict__ sidx)
-{
-    __shared__ SyrkMfmaSm<T> sm;
-    __shared__ ScreenLds<512> scr;
-    int bj, bk;
-    tile_of_block(Tt, &bj, &bk);
-    syrk_mfma_tile<T>(Xs, n, p, S, bj, bk, invn, thr, pv, scnt, sidx, sm, scr);
+    return nscr;
 }
 
 // ---------------------------------------------------------------------------
-// double form: 128 x 128 tiles.  Four waves of 64 x 64 (sixteen 16 x 16
-// accumulator blocks each): per 4-sample step a wave reads 8 operands from
-// LDS for 16 matrix-core operations, twice the 64 x 64 tile's ratio, and the
-// panels of a stage (16 samples) give 16 flops per byte read from L2.  Each
-// entry takes its products in the same sample order as the 64 x 64 kernel,
-// so S is the same to the bit.  The epilogue stages the tile through LDS in
-// two halves of 64 rows (two blocks per CU fit), each written directly and
-// transposed; a diagonal tile writes its lower-left block as the mirror of
-// its upper-right one in the first half and takes its upper triangle for
-// both halves of each diagonal block, so S is symmetric bit for bit.
+// double and float forms: operands straight from Xs into registers
+//
+// A block of four waves computes one EDGE x EDGE tile, each wave its own
+// quarter, with no LDS staging and no barrier: the 16 x 4 operands of the
+// matrix instructions are 16 consecutive variables of 4 samples, which Xs
+// (samples x variables) holds as full 128-byte (double) or 64-byte (float)
+// rows, and a wave keeps the loads of the next D - 1 steps in flight behind
+// the NB x NB operations of the current one.  Each entry takes its products
+// in sample order whatever the edge, so S is the same to the bit.
 // ---------------------------------------------------------------------------
-constexpr int kD = 128;   // tile edge
-constexpr int kDKC = 16;  // samples per stage
-constexpr int kDPad = 16; // LDS row padding of the stage panels (doubles)
-
-struct SyrkD128Sm {
-    union {
-        struct {
-            double a[kDKC][kD + kDPad];
-            double b[kDKC][kD + kDPad];
-        } in;
-        double out[64][kD + 1];  // one half of the tile
-    };
+template <typename T, int EDGE> struct SyrkShape {
+    static constexpr int NB = EDGE / 32;  // 16 x 16 blocks per wave and dimension
+    // sample steps of operands held: a step is NB x NB operations of 64
+    // (double) or 32 cycles; 128 (double): as many as leave two waves per SIMD
+    static constexpr int D = EDGE >= 128 ? (sizeof(T) == 8 ? 2 : 4) : (EDGE >= 64 ? 8 : 24);
+    typedef ScreenWaves<4, 448> Scr;
 };
 
-__device__ __forceinline__ void syrk_d128_tile(const double *__restrict__ Xs, int64_t n, int64_t p,
-                                               double *__restrict__ S, int bj, int bk, double invn, double thr,
-                                               int64_t pv, int *__restrict__ scnt, int *__restrict__ sidx,
-                                               SyrkD128Sm &sm, ScreenLds<1024> &scr)
+template <typename T, int EDGE>
+__device__ __forceinline__ void syrk_tile(const T *__restrict__ Xs, int64_t n, int64_t p, T *__restrict__ S, int bj,
+                                          int bk, T invn, T thr, int64_t pv, int *__restrict__ scnt,
+                                          int *__restrict__ sidx, typename SyrkShape<T, EDGE>::Scr &scr)
 {
-    const int64_t j0 = (int64_t)bj * kD, k0 = (int64_t)bk * kD;
-    if (threadIdx.x == 0) scr.n = 0;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    constexpr int NB = SyrkShape<T, EDGE>::NB, D = SyrkShape<T, EDGE>::D;
+    typedef typename Acc<T>::type AccT;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = w & 1, wn = w >> 1;
-    d4 acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = d4{0, 0, 0, 0};
-
-    // loader: 32 threads per sample row, 4 consecutive variables each; rows
-    // lr and lr + 8 of the stage
-    const int lr = tid >> 5, lc = (tid & 31) * 4;
-    constexpr int NL = kDKC / 8;
-    const bool even = (p & 1) == 0;  // 16-byte aligned pairs (j0, lc even)
-    double ra[NL][4], rb[NL][4];
-    auto fetch1 = [&](int64_t i, int64_t c0, double *r) {
-        if (i < n && c0 + 3 < p && even) {
-            const double2 x0 = *reinterpret_cast<const double2 *>(Xs + i * p + c0);
-            const double2 x1 = *reinterpret_cast<const double2 *>(Xs + i * p + c0 + 2);
-            r[0] = x0.x;
-            r[1] = x0.y;
-            r[2] = x1.x;
-            r[3] = x1.y;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[e] = (i < n && c0 + e < p) ? Xs[i * p + c0 + e] : 0.0;
-        }
-    };
-    auto fetch = [&](int64_t i0) {
-#pragma unroll
-        for (int h = 0; h < NL; ++h) {
-            const int64_t i = i0 + lr + 8 * h;
-            fetch1(i, j0 + lc, ra[h]);
-            fetch1(i, k0 + lc, rb[h]);
-        }
-    };
-    fetch(0);
-    for (int64_t i0 = 0; i0 < n; i0 += kDKC) {
-#pragma unroll
-        for (int h = 0; h < NL; ++h)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                sm.in.a[lr + 8 * h][lc + e] = ra[h][e];
-                sm.in.b[lr + 8 * h][lc + e] = rb[h][e];
-            }
-        __syncthreads();
-        if (i0 + kDKC < n) fetch(i0 + kDKC);  // in flight during the MFMAs below
-#pragma unroll
-        for (int kk = 0; kk < kDKC; kk += 4) {
-            double av[4], bv[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) av[a] = sm.in.a[kk + (lane >> 4)][64 * wm + 16 * a + (lane & 15)];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) bv[b] = sm.in.b[kk + (lane >> 4)][64 * wn + 16 * b + (lane & 15)];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) acc[a][b] = mfma16x16x4(av[a], bv[b], acc[a][b]);
-        }
-        __syncthreads();
-    }
-
+    const int64_t j0 = (int64_t)bj * EDGE + 16 * NB * wm, k0 = (int64_t)bk * EDGE + 16 * NB * wn;
     const bool diag = bj == bk;
-    for (int h = 0; h < 2; ++h) {
-        // rows 64h .. 64h + 63 of the tile (scaled by 1/n), from the waves
-        // that hold them
-        if (wm == h) {
+    int nscr = 0;
+    // the wave below the diagonal of a diagonal tile has nothing to store,
+    // nor has one past the last variable
+    if (j0 < p && k0 < p && !(diag && wm > wn)) {
+        const int kq = lane >> 4, c16 = lane & 15;
+        // variables past the last load that one (never stored)
+        unsigned ca[NB], cb[NB];  // p is below 2^30
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        sm.out[16 * a + acc_row<double>(lane, r)][64 * wn + 16 * b + (lane & 15)] =
-                            acc[a][b][r] * invn;
+        for (int a = 0; a < NB; ++a) {
+            const int64_t ja = j0 + 16 * a + c16, kb = k0 + 16 * a + c16;
+            ca[a] = (unsigned)(kq * p + (ja < p ? ja : p - 1));
+            cb[a] = (unsigned)(kq * p + (kb < p ? kb : p - 1));
         }
-        __syncthreads();
-        // direct rows j = j0 + 64h + rr; a diagonal tile's second half leaves
-        // columns 0..63 to the first half's mirror
-        const int c0 = (diag && h == 1) ? 64 : 0;
-        for (int e = tid; e < 64 * kD; e += 256) {
-            const int rr = e >> 7, cc = e & (kD - 1);
-            const int R = 64 * h + rr;
-            const int64_t j = j0 + R, k = k0 + cc;
-            if (cc >= c0 && j < p && k < p) {
-                double v;
-                if (j == k)
-                    v = 1.0;
-                else if (diag && R > cc)
-                    v = sm.out[cc - 64 * h][R];  // the upper-triangle value
-                else
-                    v = sm.out[rr][cc];
-                S[j * p + k] = v;
-                screen_entry(scr, scnt, sidx, thr, pv, j, k, v);
+        AccT acc[NB][NB];
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[a][b] = AccT{0, 0, 0, 0};
+        const int64_t full = n / 4;  // whole steps of 4 samples
+        T av[D][NB], bv[D][NB];
+        const T *src = Xs;  // the next step to load
+        auto load = [&](int d) {
+#pragma unroll
+            for (int a = 0; a < NB; ++a) {
+                av[d][a] = src[ca[a]];
+                bv[d][a] = src[cb[a]];
+            }
+            src += 4 * p;
+        };
+        auto mul = [&](int d) {
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[a][b] = mfma16x16x4(av[d][a], bv[d][b], acc[a][b]);
+        };
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+            if (d < full) load(d);
+        int64_t s0 = 0;
+        for (; s0 + 2 * D - 1 <= full; s0 += D) {  // every load of the round is a whole step
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                load((d + D - 1) % D);
+                mul(d);
             }
         }
-        // mirrored: S[k][j] for the half's 64 columns j; a diagonal tile
-        // mirrors only its upper-right block (first half)
-        if (!diag || h == 0) {
-            const int kc0 = diag ? 64 : 0;
-            for (int e = tid; e < kD * 64; e += 256) {
-                const int kc = e >> 6, jc = e & 63;
-                const int64_t k = k0 + kc, j = j0 + 64 * h + jc;
-                if (kc >= kc0 && j < p && k < p) {
-                    const double v = sm.out[jc][kc];
-                    S[k * p + j] = v;
-                    screen_entry(scr, scnt, sidx, thr, pv, k, j, v);
-                }
+        for (; s0 < full; s0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if (s0 + d + D - 1 < full) load((d + D - 1) % D);
+                if (s0 + d < full) mul(d);
             }
         }
-        __syncthreads();  // the half is read before the next one is staged
+        if (n % 4) {
+            const bool in = 4 * full + kq < n;
+            src = Xs + 4 * full * p;
+#pragma unroll
+            for (int a = 0; a < NB; ++a) {
+                av[0][a] = in ? src[ca[a]] : T(0);
+                bv[0][a] = in ? src[cb[a]] : T(0);
+            }
+            mul(0);
+        }
+        nscr = store_tile<T, NB, NB, false, true>(acc, S, p, j0, k0, diag, invn, thr, pv, scnt, sidx, scr, w);
     }
-    screen_flush(scr, scnt, sidx);
+    if (lane == 0) scr.n[w] = nscr;
+    __syncthreads();
+    screen_flush_waves(scr, scnt, sidx);
 }
 
-__global__ __launch_bounds__(256, 2) void k_syrk_d128(const double *__restrict__ Xs, int64_t n, int64_t p,
-                                                      double *__restrict__ S, int Tt, double invn, double thr,
-                                                      int64_t pv, int *__restrict__ scnt, int *__restrict__ sidx)
+template <typename T, int EDGE>
+__global__ __launch_bounds__(256, 2) void k_syrk(const T *__restrict__ Xs, int64_t n, int64_t p, T *__restrict__ S,
+                                              int Tt, T invn, T thr, int64_t pv, int *__restrict__ scnt,
+                                              int *__restrict__ sidx)
 {
-    __shared__ SyrkD128Sm sm;
-    __shared__ ScreenLds<1024> scr;
+    __shared__ typename SyrkShape<T, EDGE>::Scr scr;
     int bj, bk;
     tile_of_block(Tt, &bj, &bk);
-    syrk_d128_tile(Xs, n, p, S, bj, bk, invn, thr, pv, scnt, sidx, sm, scr);
-}
-
-__global__ __launch_bounds__(256, 2) void k_syrk_d128_grouped(const SyrkJobT<double> *__restrict__ tab,
-                                                              const int64_t *__restrict__ off, int nd)
-{
-    __shared__ SyrkD128Sm sm;
-    __shared__ ScreenLds<1024> scr;
-    const int64_t t = xcd_order(gridDim.x, blockIdx.x);
-    const int d = group_of(off, nd, t);
-    const SyrkJobT<double> &J = tab[d];
-    int bj, bk;
-    tri_tile(J.Tt, t - off[d], &bj, &bk);
-    syrk_d128_tile(J.Xs, J.n, J.p, J.S, bj, bk, J.invn, J.thr, J.pv, J.scnt, J.sidx, sm, scr);
-}
-
-// Tile edge of the double form: 128 when its upper-triangle tiles fill the
-// chip (at least 256), else 64 (small p: the 64 x 64 kernel keeps more CUs
-// busy).  Both kernels give each entry its products in the same sample order,
-// so S is the same to the bit either way.
-int syrk_f64_edge(int64_t p)
-{
-    const int64_t t = (p + kD - 1) / kD;
-    return t * (t + 1) / 2 >= 256 ? kD : 64;
+    syrk_tile<T, EDGE>(Xs, n, p, S, bj, bk, invn, thr, pv, scnt, sidx, scr);
 }
 
 // The tiles of many problems in one launch, one tile per block: block b
 // (in the XCD-aware order) is tile b - off[d] of problem d.
-template <typename T>
-__global__ __launch_bounds__(256) void k_syrk_mfma_grouped(const SyrkJobT<T> *__restrict__ tab,
-                                                           const int64_t *__restrict__ off, int nd)
+template <typename T, int EDGE>
+__global__ __launch_bounds__(256, 2) void k_syrk_grouped(const SyrkJobT<T> *__restrict__ tab,
+                                                      const int64_t *__restrict__ off, int nd)
 {
-    __shared__ SyrkMfmaSm<T> sm;
-    __shared__ ScreenLds<512> scr;
+    __shared__ typename SyrkShape<T, EDGE>::Scr scr;
     const int64_t t = xcd_order(gridDim.x, blockIdx.x);
     const int d = group_of(off, nd, t);
     const SyrkJobT<T> &J = tab[d];
     int bj, bk;
     tri_tile(J.Tt, t - off[d], &bj, &bk);
-    syrk_mfma_tile<T>(J.Xs, J.n, J.p, J.S, bj, bk, J.invn, J.thr, J.pv, J.scnt, J.sidx, sm, scr);
+    syrk_tile<T, EDGE>(J.Xs, J.n, J.p, J.S, bj, bk, J.invn, J.thr, J.pv, J.scnt, J.sidx, scr);
+}
+
+// Tile edge of the double (dbl) and float forms from the launch's numbers of
+// 64 x 64 and 128 x 128 tiles (every edge gives the same bits).  Measured, in
+// us, edges 32 / 64 / 128 (n x p, no screen), and the LDS-staged kernels these
+// replaced (64 below 256 tiles of 128, then 128; float 64):
+//   double 100 x 200      7.5 /  9.6 /  24             (start 9.9)
+//   double 1500 x 300     30 /   62 / 197               (105)
+//   double 250 x 756      15 /   17 /  44               (25)
+//   double 200 x 1000     18 /   16 /  38               (23)
+//   double 400 x 5000    326 /  234 / 235               (283)
+//   double 1000 x 5000   738 /  491 / 531               (625)
+//   double 1000 x 10000 2756 / 1835 / 1707              (2010)
+//   float 1500 x 300      20 /   46 / 136               (70)
+//   float 200 x 1000      13 /   13 /  29               (18)
+//   float 333 x 2047      39 /   37 /  45               (45)
+//   float 400 x 5000     197 /  162 / 158               (191)
+//   float 1000 x 10000  1635 / 1348 / 1142              (1508)
+// Few tiles leave SIMDs idle behind a serial chain of n / 4 steps, so they are
+// cut smaller; many are bound by the operands' traffic from L2 (64: about
+// 16 bytes per cycle and CU beside the matrix cores), so they are cut larger.
+int syrk_edge(int64_t tiles64, int64_t tiles128, bool dbl)
+{
+    if (tiles64 < 120) return 32;
+    return tiles128 >= (dbl ? 2000 : 800) ? 128 : 64;
 }
 
 template <typename T>
@@ -582,11 +392,12 @@ void launch_syrk_mfma_grouped(const SyrkJobT<T> *tab, const int64_t *tile_off, i
                               hipStream_t s)
 {
     if (tiles <= 0) return;
-    if (sizeof(T) == 8 && edge == kD)
-        hipLaunchKernelGGL(k_syrk_d128_grouped, dim3((unsigned)tiles), dim3(256), 0, s,
-                           (const SyrkJobT<double> *)tab, tile_off, nd);
+    if (edge == 128)
+        hipLaunchKernelGGL((k_syrk_grouped<T, 128>), dim3((unsigned)tiles), dim3(256), 0, s, tab, tile_off, nd);
+    else if (edge == 32)
+        hipLaunchKernelGGL((k_syrk_grouped<T, 32>), dim3((unsigned)tiles), dim3(256), 0, s, tab, tile_off, nd);
     else
-        hipLaunchKernelGGL(k_syrk_mfma_grouped<T>, dim3((unsigned)tiles), dim3(256), 0, s, tab, tile_off, nd);
+        hipLaunchKernelGGL((k_syrk_grouped<T, 64>), dim3((unsigned)tiles), dim3(256), 0, s, tab, tile_off, nd);
 }
 
 template SyrkJobT<double> syrk_job_mfma<double>(const double *, int64_t, int64_t, double *, const Screen &, int,
@@ -601,15 +412,18 @@ template void launch_syrk_mfma_grouped<float>(const SyrkJobT<float> *, const int
 template <typename T>
 static void launch_syrk_t(const T *Xs, int64_t n, int64_t p, T *S, T thr, const Screen &sc, hipStream_t s)
 {
-    const int edge = sizeof(T) == 8 ? syrk_f64_edge(p) : 64;
+    const int64_t t64 = (p + 63) / 64, t128 = (p + 127) / 128;
+    const int edge = syrk_edge(t64 * (t64 + 1) / 2, t128 * (t128 + 1) / 2, sizeof(T) == 8);
     const int Tt = (int)((p + edge - 1) / edge);
-    const int64_t ntiles = (int64_t)Tt * (Tt + 1) / 2;
-    if (sizeof(T) == 8 && edge == kD)
-        hipLaunchKernelGGL(k_syrk_d128, dim3((unsigned)ntiles), dim3(256), 0, s, (const double *)Xs, n, p,
-                           (double *)S, Tt, 1.0 / (double)n, (double)thr, sc.pv > 0 ? sc.pv : p, sc.cnt, sc.idx);
+    const dim3 grid((unsigned)((int64_t)Tt * (Tt + 1) / 2));
+    const T invn = (T)(1.0 / (double)n);
+    const int64_t pv = sc.pv > 0 ? sc.pv : p;
+    if (edge == 128)
+        hipLaunchKernelGGL((k_syrk<T, 128>), grid, dim3(256), 0, s, Xs, n, p, S, Tt, invn, thr, pv, sc.cnt, sc.idx);
+    else if (edge == 32)
+        hipLaunchKernelGGL((k_syrk<T, 32>), grid, dim3(256), 0, s, Xs, n, p, S, Tt, invn, thr, pv, sc.cnt, sc.idx);
     else
-        hipLaunchKernelGGL(k_syrk_mfma<T>, dim3((unsigned)ntiles), dim3(256), 0, s, Xs, n, p, S, Tt,
-                           (T)(1.0 / (double)n), thr, sc.pv > 0 ? sc.pv : p, sc.cnt, sc.idx);
+        hipLaunchKernelGGL((k_syrk<T, 64>), grid, dim3(256), 0, s, Xs, n, p, S, Tt, invn, thr, pv, sc.cnt, sc.idx);
 }
 
 void launch_syrk_f64(const double *Xs, int64_t n, int64_t p, double *S, const Screen &sc, hipStream_t s)
@@ -638,60 +452,6 @@ __device__ __forceinline__ f4 bf_mma(bf8 ha, bf8 la, bf8 hb, bf8 lb, f4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha, hb, c, 0, 0, 0);
 }
 
-template <bool NT, typename V> __device__ __forceinline__ void store_s(V *at, V v)
-{
-    if constexpr (NT) __builtin_nontemporal_store(v, at);
-    else *at = v;
-}
-
-// A wave's NA x NB accumulator blocks (from variable j0 / k0 of S) to S and
-// the screen, straight from the accumulators: lane l holds rows jb .. jb + 3
-// (jb = 4 (l / 16) within the 16 x 16 block) of column kk = l % 16.  Direct:
-// 16 lanes store 64 consecutive bytes of a row of S; mirrored: the lane's
-// four rows are four consecutive columns of row kk, one 16-byte store.  A
-// diagonal tile stores its upper triangle both ways, so S is symmetric bit
-// for bit.  Returns the wave's count of screen entries.
-// NT: nontemporal stores.
-template <int NA, int NB, bool NT, typename SCR>
-__device__ __forceinline__ int bf_store(const f4 (&acc)[NA][NB], float *__restrict__ S, int64_t p, int64_t j0,
-                                        int64_t k0, bool diag, float invn, float thr, int *__restrict__ scnt,
-                                        int *__restrict__ sidx, SCR &scr, int w)
-{
-    const int lane = threadIdx.x & 63;
-    const int g4 = 4 * (lane >> 4), c16 = lane & 15;
-    const bool vec_ok = (p & 3) == 0;  // rows of S 16-byte aligned
-    int nscr = 0;
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int64_t kk = k0 + 16 * b + c16;
-            const int64_t jb = j0 + 16 * a + g4;
-            float v[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = jb + r == kk ? 1.0f : acc[a][b][r] * invn;
-            // screen: a pair above the threshold is a candidate of both
-            // columns (every lane takes part in the ballots)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const bool mine = jb + r < p && kk < p && (!diag || jb + r < kk);
-                screen_pair_wave(scr, w, nscr, scnt, sidx, thr, jb + r, kk, mine ? v[r] : 0.0f);
-            }
-            if (kk >= p) continue;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (jb + r < p && (!diag || jb + r <= kk)) store_s<NT>(&S[(jb + r) * p + kk], v[r]);
-            if (vec_ok && jb + 3 < p && (!diag || kk > jb + 3)) {
-                store_s<NT>(reinterpret_cast<f4 *>(&S[kk * p + jb]), f4{v[0], v[1], v[2], v[3]});
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (jb + r < p && (!diag || kk > jb + r)) store_s<NT>(&S[kk * p + jb + r], v[r]);
-            }
-        }
-    return nscr;
-}
-
 // --- 64 x 64 tiles: operands straight into registers ----------------------
 // A block of four waves, each its own 32 x 32 quarter, with no LDS staging
 // and no barrier: a wave keeps the loads of the next three steps (8 operands
@@ -707,7 +467,7 @@ __device__ __forceinline__ void bf_tile64(const uint16_t *__restrict__ split, in
                                           int *__restrict__ sidx, int bj, int bk, BfScreen64 &scr)
 {
     constexpr int NB = 2, D = 4;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = w & 1, wn = w >> 1;
     const int ks = (int)(npad / kBfKC);
     const int64_t j0 = (int64_t)bj * kBfSmall + 32 * wm, k0 = (int64_t)bk * kBfSmall + 32 * wn;
@@ -722,8 +482,8 @@ __device__ __forceinline__ void bf_tile64(const uint16_t *__restrict__ split, in
         for (int a = 0; a < NB; ++a) {
             // row blocks past the last load that one (never stored)
             const int64_t ra = j0 / 16 + a, rb = k0 / 16 + a;
-            pa[a] = reinterpret_cast<const bf8 *>(split) + (ra < rbs ? ra : rbs - 1) * ks * 128 + lane;
-            pb[a] = reinterpret_cast<const bf8 *>(split) + (rb < rbs ? rb : rbs - 1) * ks * 128 + lane;
+            pa[a] = reinterpret_cast<const bf8 *>(split) + (ra < rbs ? ra : rbs - 1) * ks * 128;
+            pb[a] = reinterpret_cast<const bf8 *>(split) + (rb < rbs ? rb : rbs - 1) * ks * 128;
         }
         f4 acc[NB][NB];
 #pragma unroll
@@ -735,10 +495,10 @@ __device__ __forceinline__ void bf_tile64(const uint16_t *__restrict__ split, in
             const int64_t o = (int64_t)(st < ks ? st : ks - 1) * 128;
 #pragma unroll
             for (int a = 0; a < NB; ++a) {
-                ha[d][a] = pa[a][o];
-                la[d][a] = pa[a][o + 64];
-                hb[d][a] = pb[a][o];
-                lb[d][a] = pb[a][o + 64];
+                ha[d][a] = (pa[a] + o)[lane];
+                la[d][a] = (pa[a] + o + 64)[lane];
+                hb[d][a] = (pb[a] + o)[lane];
+                lb[d][a] = (pb[a] + o + 64)[lane];
             }
         };
 #pragma unroll
@@ -756,7 +516,7 @@ __device__ __forceinline__ void bf_tile64(const uint16_t *__restrict__ split, in
                 }
             }
         }
-        nscr = bf_store<NB, NB, false>(acc, S, p, j0, k0, diag, invn, thr, scnt, sidx, scr, w);
+        nscr = store_tile<float, NB, NB, false, false>(acc, S, p, j0, k0, diag, invn, thr, p, scnt, sidx, scr, w);
     }
     if (lane == 0) scr.n[w] = nscr;
     __syncthreads();
@@ -813,7 +573,7 @@ static_assert(kBfLds <= 160 * 1024, "LDS of one block");
 __device__ __forceinline__ void bf_issue(const uint16_t *__restrict__ split, int ks, int64_t rbs, int64_t rj,
                                          int64_t rk, int st, bool diag, unsigned char *stage)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // wave wv copies row blocks wv and wv + 8 of each panel, hi and lo
     const int npan = diag ? 1 : 2;
     for (int pnl = 0; pnl < npan; ++pnl)
@@ -839,7 +599,7 @@ __device__ __forceinline__ void bf_tile256(const uint16_t *__restrict__ split, i
                                            int *__restrict__ sidx, int bj, int bk, unsigned char *bf_lds)
 {
     BfScreen &scr = *reinterpret_cast<BfScreen *>(bf_lds + 2 * kBfStage);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = w & 3, wn = w >> 2;
     const int ks = (int)(npad / kBfKC);  // even
     const int64_t rbs = (p + 15) / 16;
@@ -905,7 +665,8 @@ __device__ __forceinline__ void bf_tile256(const uint16_t *__restrict__ split, i
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    const int nscr = bf_store<4, 8, NT>(acc, S, p, j0 + 64 * wm, k0 + 128 * wn, diag, invn, thr, scnt, sidx, scr, w);
+    const int nscr = store_tile<float, 4, 8, NT, false>(acc, S, p, j0 + 64 * wm, k0 + 128 * wn, diag, invn, thr, p, scnt,
+                                                 sidx, scr, w);
     if (lane == 0) scr.n[w] = nscr;
     __syncthreads();
     screen_flush_waves(scr, scnt, sidx);
