@@ -116,7 +116,7 @@ struct Bump {
 // The data form (SPMESL_FLAG_DATA_FORM, double): no S.  The standardised
 // data Xt, the per-column lists, and the dense tier's workspace for
 // kDataGroups workgroups whose V holds up to kDataVcap rows.
-constexpr int kDataGroups = 128;
+constexpr int kDataGroups = 256;
 constexpr int64_t kDataVcap = 1024;  // V beyond it fails (S_VV of 8 MB per workgroup)
 
 Plan make_plan_data(int64_t n, int64_t p)
@@ -158,7 +158,7 @@ Plan make_plan_data(int64_t n, int64_t p)
     L.dsk = b.take(8 * 16 * G * VC);
     L.svv_cap = L.dvcap;
     L.dsvv = b.take(8 * G * VC * VC);
-    L.de = b.take(8 * 16 * N * G);
+    L.de = b.take(8 * 16 * ((N + 31) / 32 * 32) * G);
     L.total = b.cur;
     return L;
 }
@@ -178,7 +178,7 @@ Plan make_plan(int64_t n, int64_t p, int prec, bool data = false)
     const Plan one = make_plan_g(n, p, prec, 1);
     const size_t P = (size_t)p;
     size_t slice = 4 * P + 8 * P + 4 * 8 * 16 * P;
-    if (prec == SPMESL_MIXED) slice += 8 * (size_t)one.svv_cap * (size_t)one.svv_cap + 8 * 16 * (size_t)n;
+    if (prec == SPMESL_MIXED) slice += 8 * (size_t)one.svv_cap * (size_t)one.svv_cap + 8 * 16 * (((size_t)n + 31) / 32 * 32);
     const size_t budget = std::max(kDenseBudgetFloor, one.total / 4);
     const int G = (int)std::min<size_t>(kDenseGroupsMax, std::max<size_t>(1, budget / slice));
     return G == 1 ? one : make_plan_g(n, p, prec, G);
@@ -254,7 +254,7 @@ Plan make_plan_g(int64_t n, int64_t p, int prec, int G)
         // S[V, V] of the double dense tier (formed from the data)
         L.svv_cap = p < kDenseDataMax ? p : kDenseDataMax;
         L.dsvv = b.take(8 * (size_t)L.svv_cap * (size_t)L.svv_cap * GG);
-        L.de = b.take(8 * 16 * N * GG);
+        L.de = b.take(8 * 16 * ((N + 31) / 32 * 32) * GG);
         L.sigma64 = b.take(8 * P);
         L.lam64 = b.take(8 * P);
         L.cstat64 = b.take(4 * P);

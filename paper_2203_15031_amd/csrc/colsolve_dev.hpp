@@ -85,9 +85,14 @@ __device__ __forceinline__ float soft_clamp(float a, float lam)
 {
     return a - __builtin_amdgcn_fmed3f(a, -lam, lam);
 }
+// (the two instructions as they are: fmin and fmax would re-canonicalise
+// lam in every step of a sweep)
 __device__ __forceinline__ double soft_clamp(double a, double lam)
 {
-    return a - fmax(fmin(a, lam), -lam);
+    double c;
+    asm("v_min_f64 %0, %1, %2" : "=v"(c) : "v"(a), "v"(lam));
+    asm("v_max_f64 %0, %1, -%2" : "=v"(c) : "v"(c), "v"(lam));
+    return a - c;
 }
 
 // lower_bound over an ascending int array in LDS

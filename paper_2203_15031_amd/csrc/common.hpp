@@ -352,7 +352,7 @@ struct DenseArgs {
     int64_t vcap;         // the most rows V may hold (a group beyond it fails)
     double *Svv;          // [svv_cap^2] per slice (data source)
     int64_t svv_cap;
-    double *E;            // [16 * n] per slice (data source)
+    double *E;            // [16 * (n rounded up to 32)] per slice (data source)
     unsigned long long *counters;
     const int *flags;
 };
