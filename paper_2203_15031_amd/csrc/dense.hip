@@ -46,8 +46,8 @@
 // Measured, against 8 waves with gradients and coefficients in global memory
 // and each operand waited for:
 //   n = 1500, p = 300, double (19 groups, V about 300): a group's sweeps and
-//     updates 10.9 -> 6.1 ms, the solve 15.9 -> 11.6 ms (3.4 ms of it the LDS
-//     tiers); with 8 waves of 256 registers 5.4 ms, but the full gradient slower;
+//     updates 10.9 -> 6.1 ms, the solve 15.9 -> 11.6 ms, and 8.6 with the LDS tiers'
+//     shorter steps; with 8 waves of 256 registers 5.4 ms, but the full gradient slower;
 //   n = 400, p = 2500, data form (157 groups, V about 40): 6.0 -> 1.2 ms a
 //     solve: a group's iterations 450 -> 40 us, a full gradient 870 -> 290 us
 //     (its 2 GB of Xt reads a pass come from the caches at 4.4 TB/s).
@@ -214,7 +214,7 @@ struct DenseSm {
 // Block-wide compaction of the rows marked in `mark` (in ascending order)
 // into V; every marked row becomes 1.  Returns |V|.
 template <typename T>
-__device__ __forceinline__ int build_v(const DenseArgs<T> &A, DenseSm<T> &sm)
+__device__ __forceinline__ int compact_v(const DenseArgs<T> &A, DenseSm<T> &sm)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     int base = 0;
@@ -237,6 +237,21 @@ __device__ __forceinline__ int build_v(const DenseArgs<T> &A, DenseSm<T> &sm)
         __syncthreads();
     }
     return base;
+}
+
+// V from the marks; when it covers 15/16 of all rows (and at most `cap` rows
+// fit) the others are taken as well.  A row that a full gradient adds later
+// costs the group a new S on V and all its sweeps again, where a row too many
+// costs at most 1/8 more per sweep; and with every row in V, no result depends
+// on which columns the queue's order puts into a group.
+template <typename T>
+__device__ __forceinline__ int build_v(const DenseArgs<T> &A, DenseSm<T> &sm, int64_t cap)
+{
+    const int nv = compact_v(A, sm);
+    if (nv >= A.p || A.p > cap || 16 * (int64_t)nv < 15 * A.p) return nv;
+    for (int64_t j = threadIdx.x; j < A.p; j += kDT) A.mark[j] = 1;
+    __syncthreads();
+    return compact_v(A, sm);
 }
 
 // position of row j in V[0 .. nv) (j is in V)
@@ -560,29 +575,6 @@ __device__ __forceinline__ NoiseStep<T> noise_step(const DenseArgs<T> &A, T so, 
     return o;
 }
 
-// One column's sweep over the coordinates of the lanes in `live`, in order:
-// r the lane's gradient, beta its coefficient, sjj[j][lane] the entry of S
-// between coordinate j and the lane's.
-template <typename T>
-__device__ __forceinline__ void sweep_lanes(const T (*sjj)[kBMax + 1], T lam, unsigned long long live, T &r, T &beta)
-{
-    const int lane = lane_id();
-    T nb = soft_clamp(r + beta, lam);
-    T d = nb - beta;
-    unsigned long long mk = __ballot(d != T(0)) & live;
-    while (mk) {
-        const int j = __builtin_ctzll(mk);
-        const T row = sjj[j][lane];
-        const T dd = bcast(d, j);
-        if (lane == j) beta = nb;
-        r -= row * dd;
-        live &= ~1ull << j;  // the coordinates after j
-        nb = soft_clamp(r + beta, lam);
-        d = nb - beta;
-        mk = __ballot(d != T(0)) & live;
-    }
-}
-
 // V of up to kBMax rows: one block, so every column's whole iteration runs in
 // its own wave (one lane per row of V, S[V, V] in LDS), with no barrier until
 // all are done.  A.Bd holds the coefficients before and after.
@@ -616,7 +608,7 @@ __device__ __forceinline__ void run_small(const DenseArgs<T> &A, DenseSm<T> &sm,
             }
             for (;;) {
                 const T beta0 = beta;
-                sweep_lanes(sm.sjj, lam, lanes, r, beta);
+                sweep_lanes(lam, lanes, r, beta, [&](int j, T d) { r -= sm.sjj[j][lane] * d; });
                 const T dl = beta - beta0;  // each coordinate changes at most once
                 updates += __popcll(__ballot(dl != T(0)));
                 ++sweeps;
@@ -731,7 +723,7 @@ __device__ __forceinline__ void run_sweeps(const DenseArgs<T> &A, DenseSm<T> &sm
                 T r = R[e];
                 const T beta0 = act ? B[e] : T(0);
                 T beta = beta0;
-                sweep_lanes(sm.sjj, lam, __ballot(act), r, beta);
+                sweep_lanes(lam, __ballot(act), r, beta, [&](int j, T d) { r -= sm.sjj[j][lane] * d; });
                 dl = act ? beta - beta0 : T(0);  // each coordinate changes at most once
                 nupd += __popcll(__ballot(dl != T(0)));
                 over |= __ballot((dl < T(0) ? -dl : dl) >= A.tol) != 0ull;
@@ -955,7 +947,7 @@ __global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src
             }
         }
         __syncthreads();
-        int nv = build_v(A, sm);
+        int nv = build_v(A, sm, vlim);
         bool gfail = false;
         if ((int64_t)nv > vlim) {
             // V does not fit this workgroup's buffers: the group fails (rare)
@@ -1017,7 +1009,7 @@ __global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src
             for (int64_t e = tid; e < (int64_t)nv_old * kDW; e += kDT) A.R[e] = A.Bd[e];
             for (int64_t e = tid; e < (int64_t)nv_old; e += kDT) A.Vold[e] = A.V[e];
             __syncthreads();
-            nv = build_v(A, sm);
+            nv = build_v(A, sm, vlim);
             if (tid < m) {
                 sm.added[tid] += nv - nv_old;
                 sm.have[tid] = 0;  // B moved: the secant needs two fresh updates again
