@@ -8,17 +8,23 @@
 // the coefficients of response k) into the per-column working sets the
 // column solves resume from.
 //
-// A block owns 64 consecutive columns (one lane each) and splits the rows
-// of B0 over its 16 waves in contiguous ranges, so every load is a coalesced
-// row segment.  Two passes over the block's column strip: the first counts
-// each wave's nonzeros per column, the second writes them at the offsets of
-// an exclusive scan over the waves, so each column's list is in ascending
-// row order (the order the solver keeps its working sets in).
+// A block owns 16 consecutive columns, whose rows are split over 64 segments:
+// 16 waves of four, a lane per column and segment, so a load takes 128
+// consecutive bytes of four rows.  Two passes over the block's column strip:
+// the first counts each segment's nonzeros per column, the second (out of the
+// caches) writes them at the offsets of a scan over the segments, so each
+// column's list is in ascending row order (the order the solver keeps its
+// working sets in).  What bounds it is the latency of B0's reads: with 64
+// columns per block, p = 2000 had 32 blocks and one load per wave in flight
+// (155 us); with 125 blocks and 16 rows of a lane in flight 18 us.
 #include "common.hpp"
 
 namespace spmesl {
 
 constexpr int kWarmWaves = 16;
+constexpr int kWarmCols = 16;                                   // columns per block
+constexpr int kWarmSegs = kWarmWaves * (kWave / kWarmCols);     // row segments of a column
+constexpr int kWarmRows = 16;                                   // rows of a lane in flight
 
 template <typename T>
 __global__ __launch_bounds__(kWave *kWarmWaves) void k_warm_start(
@@ -27,40 +33,57 @@ __global__ __launch_bounds__(kWave *kWarmWaves) void k_warm_start(
     int *__restrict__ w_idx, T *__restrict__ w_beta, double *__restrict__ sigma,
     double *__restrict__ lam_used, int *__restrict__ col_status)
 {
-    __shared__ int cnt[kWarmWaves][kWave];
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    const int64_t k = (int64_t)blockIdx.x * kWave + lane;
+    __shared__ int cnt[kWarmSegs][kWarmCols];
+    const int c = threadIdx.x & (kWarmCols - 1), seg = threadIdx.x / kWarmCols;
+    const int64_t k = (int64_t)blockIdx.x * kWarmCols + c;
     const bool col = k < p;
-    const int64_t rows = (p + kWarmWaves - 1) / kWarmWaves;
-    const int64_t j0 = (int64_t)wv * rows;
+    const int64_t kc = col ? k : p - 1;
+    const int64_t rows = (p + kWarmSegs - 1) / kWarmSegs;
+    const int64_t j0 = (int64_t)seg * rows;
     const int64_t j1 = j0 + rows < p ? j0 + rows : p;
-    const double ck = col ? scale[k] : 1.0;
+    const double ck = scale[kc];
     // the value stored for (j, k), or 0 when (j, k) is not kept
     auto value = [&](int64_t j, double b) -> T {
         if (j == k || b == 0.0) return T(0);
         const double v = original ? b * ck / scale[j] : b;
         return (T)v;
     };
-    int c = 0;
-    if (B0 && col)
-        for (int64_t j = j0; j < j1; ++j) c += value(j, B0[j * p + k]) != T(0);
-    cnt[wv][lane] = c;
-    __syncthreads();
-    int off = 0, tot = 0;
-    for (int w = 0; w < kWarmWaves; ++w) {
-        off += w < wv ? cnt[w][lane] : 0;
-        tot += cnt[w][lane];
-    }
-    if (B0 && col && off < kWMax)
-        for (int64_t j = j0; j < j1 && off < kWMax; ++j) {
-            const T v = value(j, B0[j * p + k]);
-            if (v != T(0)) {
-                w_idx[k * kWMax + off] = (int)j;
-                w_beta[k * kWMax + off] = v;
-                ++off;
+    // f(j, value) for the kept entries of the segment, in order
+    auto each = [&](auto f) {
+        for (int64_t j = j0; j < j1; j += kWarmRows) {
+            double b[kWarmRows];
+#pragma unroll
+            for (int u = 0; u < kWarmRows; ++u) b[u] = B0[(j + u < p ? j + u : p - 1) * p + kc];
+            unsigned nz = 0u;
+#pragma unroll
+            for (int u = 0; u < kWarmRows; ++u) nz |= b[u] != 0.0 && j + u < j1 ? 1u << u : 0u;
+            for (; nz; nz &= nz - 1) {  // (few: read again rather than indexed)
+                const int64_t ju = j + __builtin_ctz(nz);
+                const T v = value(ju, B0[ju * p + kc]);
+                if (v != T(0)) f(ju, v);
             }
         }
-    if (wv == 0 && col) {
+    };
+    int own = 0;
+    if (B0) each([&](int64_t, T) { ++own; });
+    cnt[seg][c] = own;
+    __syncthreads();
+    int off = 0, tot = 0;
+#pragma unroll 8
+    for (int g = 0; g < kWarmSegs; ++g) {
+        const int x = cnt[g][c];
+        off += g < seg ? x : 0;
+        tot += x;
+    }
+    if (col && own > 0 && off < kWMax)
+        each([&](int64_t j, T v) {
+            if (off < kWMax) {
+                w_idx[k * kWMax + off] = (int)j;
+                w_beta[k * kWMax + off] = v;
+            }
+            ++off;
+        });
+    if (seg == 0 && col) {
         double sg = 1.0;
         if (sigma0) {
             const double v = original ? sigma0[k] * ck : sigma0[k];
@@ -78,7 +101,7 @@ void launch_warm_start(const double *B0, const double *sigma0, int64_t p, const 
                        double lambda0, int *w_cnt, int *w_idx, T *w_beta, double *sigma, double *lam_used,
                        int *col_status, hipStream_t s)
 {
-    const unsigned blocks = (unsigned)((p + kWave - 1) / kWave);
+    const unsigned blocks = (unsigned)((p + kWarmCols - 1) / kWarmCols);
     hipLaunchKernelGGL(k_warm_start<T>, dim3(blocks), dim3(kWave * kWarmWaves), 0, s, B0, sigma0, p, scale,
                        original, lambda0, w_cnt, w_idx, w_beta, sigma, lam_used, col_status);
 }
