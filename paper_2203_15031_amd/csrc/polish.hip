@@ -88,74 +88,131 @@ __device__ __forceinline__ void store_gram_rows(WaveSm<double, LW> &sm, int w, c
 constexpr int kSmallW = 3;   // four rows, four chunks per batch
 constexpr int kMidW = 7;     // eight rows, two chunks per batch
 
-// Larger working sets: the rows x_k, x_{W'[0]}, .. (R = w + 1 of them) in
-// blocks of four; each pair of blocks reads its eight rows for two 64-sample
-// chunks at a time (all loads of a step in flight) and accumulates the 16
-// products in registers, so a row is re-read once per block rather than once
-// per pair.  Products of rows a < b go to s_W' (a = 0, staged in tbeta) or to
-// S_W'W' (mirrored), divided by n.
+// Larger working sets: the Gram matrix of the rows x_k, x_{W'[0]}, ..
+// (R = w + 1 of them) on the matrix cores, 16 x 16 products at a time.  Lane
+// l supplies row l % 16 of a block of 16 and takes the samples in pairs: 8 u +
+// 2 (l / 16) and the next, so four lanes read 64 consecutive bytes of a row,
+// and one product takes the even, one the odd samples of every 8.
+typedef double gpair __attribute__((ext_vector_type(2), aligned(8)));  // (rows are 8-byte aligned)
+typedef double gacc __attribute__((ext_vector_type(4)));
+
+// acc of the NB (NB + 1) / 2 products of NB row blocks (of the blocks with
+// themselves), or of NB / 2 blocks with the other NB / 2 (OFF), over n samples;
+// U pairs of a lane and row in flight.
+template <int NB, bool OFF, int U, int NT>
+__device__ __forceinline__ void gram_products(const double *const (&row)[NB], int64_t n, gacc (&acc)[NT])
+{
+    const int kq = 2 * (lane_id() >> 4);
+    static_assert(NB <= 2 || OFF, "products numbered for one or two blocks");
+    auto step = [&](const gpair (&v)[U][NB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int a = 0; a < (OFF ? NB / 2 : NB); ++a)
+#pragma unroll
+                    for (int b = OFF ? NB / 2 : a; b < NB; ++b) {
+                        const int t = OFF ? NB / 2 * a + b - NB / 2 : a + b;
+                        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[u][a][x], v[u][b][x], acc[t], 0, 0, 0);
+                    }
+    };
+    int64_t i0 = 0;
+    for (; i0 + 8 * U <= n; i0 += 8 * U) {
+        gpair v[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < NB; ++q) v[u][q] = *reinterpret_cast<const gpair *>(row[q] + i0 + 8 * u + kq);
+        step(v);
+    }
+    if (i0 < n) {
+        gpair v[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + 8 * u + kq, c0 = i < n ? i : n - 1, c1 = i + 1 < n ? i + 1 : n - 1;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const double x = row[q][c0], y = row[q][c1];
+                v[u][q] = gpair{i < n ? x : 0.0, i + 1 < n ? y : 0.0};
+            }
+        }
+        step(v);
+    }
+}
+
+// Products of rows a < b go to s_W' (a = 0, staged in tbeta) or to S_W'W'
+// (mirrored), divided by n: one or two blocks of 16 rows with themselves, then
+// with later ones.  What it replaces, four rows with four in the lanes and
+// sums over the lanes of each of the 16 products, was bound by those sums and
+// the loads between them; a product's chain here is n / 4 matrix instructions
+// of 64 cycles.  Polish kernels, before -> now: n = 250, p = 500 (hub networks,
+// W' up to 30) 88 -> 54 us; n = 1000, p = 20000 333 -> 167 us, and its columns
+// of 33 to 63 coordinates 779 -> 174 us; n = 400, p = 5000 (W' up to 7: the
+// paths above) 31 -> 32 us.
 template <int LW>
-__device__ void gram_blocked(const double *__restrict__ Xt, int64_t n, int64_t p, int64_t k,
-                             WaveSm<double, LW> &sm, int w)
+__device__ __forceinline__ void gram_tiles(const double *__restrict__ Xt, int64_t n, int64_t p, int64_t k,
+                                           WaveSm<double, LW> &sm, int w)
 {
     const int lane = lane_id();
-    const int R = w + 1;
-    const int nb = (R + 3) / 4;
+    const int nb = (w + 1 + 15) / 16;
     const double invn = 1.0 / (double)n;
-    auto row = [&](int r) -> const double * {
+    auto row = [&](int blk) -> const double * {
+        const int r = 16 * blk + (lane & 15);
         return Xt + (r == 0 || r > w ? k : clamp_index(sm.widx[r - 1], p)) * n;
     };
-    for (int bi = 0; bi < nb; ++bi)
-        for (int bj = bi; bj < nb; ++bj) {
-            const double *ra[4], *rb[4];
-            bool va[4], vb[4];
+    // lane l holds rows 4 r + l / 16 of column l % 16 of a product
+    auto put = [&](gacc d, int bi, int bj) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                va[u] = 4 * bi + u < R;
-                vb[u] = 4 * bj + u < R;
-                ra[u] = row(4 * bi + u);
-                rb[u] = row(4 * bj + u);
-            }
-            double acc[4][4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = 0.0;
-            for (int64_t i0 = lane; i0 < n; i0 += 2 * kWave) {
-                double xa[2][4], xb[2][4];
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int64_t i = i0 + c * kWave;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        xa[c][u] = (va[u] && i < n) ? ra[u][i] : 0.0;
-                        xb[c][u] = (vb[u] && i < n) ? rb[u][i] : 0.0;
-                    }
+        for (int r = 0; r < 4; ++r) {
+            const int a = 16 * bi + 4 * r + (lane >> 4), b = 16 * bj + (lane & 15);
+            if (a < b && b <= w) {
+                const double val = d[r] * invn;
+                if (a == 0) {
+                    sm.tbeta[b - 1] = val;
+                } else {
+                    sm.sww[(b - 1) * LW + (a - 1)] = val;
+                    sm.sww[(a - 1) * LW + (b - 1)] = val;
                 }
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[u][v] += xa[c][u] * xb[c][v];
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int a = 4 * bi + u, b = 4 * bj + v;
-                    if (!(a < b && b < R)) continue;  // wave-uniform
-                    const double val = wave_sum(acc[u][v]) * invn;
-                    if (lane == 0) {
-                        if (a == 0) {
-                            sm.tbeta[b - 1] = val;
-                        } else {
-                            sm.sww[(b - 1) * LW + (a - 1)] = val;
-                            sm.sww[(a - 1) * LW + (b - 1)] = val;
-                        }
-                    }
-                }
         }
+    };
+    const gacc zero = {0.0, 0.0, 0.0, 0.0};
+    constexpr int U1 = LW > 32 ? 8 : 4, U2 = LW > 32 ? 4 : 2;  // (three waves per SIMD at 32)
+    for (int bi = 0; bi < nb; bi += 2) {
+        if (bi + 1 == nb) {
+            const double *r[1] = {row(bi)};
+            gacc acc[1] = {zero};
+            gram_products<1, false, U1>(r, n, acc);
+            put(acc[0], bi, bi);
+        } else {
+            const double *r[2] = {row(bi), row(bi + 1)};
+            gacc acc[3] = {zero, zero, zero};
+            gram_products<2, false, U2>(r, n, acc);
+            put(acc[0], bi, bi);
+            put(acc[1], bi, bi + 1);
+            put(acc[2], bi + 1, bi + 1);
+        }
+        for (int bj = bi + 2; bj < nb; bj += 2) {
+            if constexpr (LW > 32) {
+                // (a block past the last repeats x_k: its products are not stored)
+                const double *r[4] = {row(bi), row(bi + 1), row(bj), row(bj + 1)};
+                gacc acc[4] = {zero, zero, zero, zero};
+                gram_products<4, true, 4>(r, n, acc);
+                put(acc[0], bi, bj);
+                put(acc[1], bi, bj + 1);
+                put(acc[2], bi + 1, bj);
+                put(acc[3], bi + 1, bj + 1);
+            } else {
+                for (int b = bi; b < bi + 2; ++b) {  // W' of 32: the last block's one row
+                    const double *r[2] = {row(b), row(bj)};
+                    gacc acc[1] = {zero};
+                    gram_products<2, true, U2>(r, n, acc);
+                    put(acc[0], b, bj);
+                }
+            }
+        }
+    }
 }
 
 template <int LW>
@@ -175,7 +232,7 @@ __device__ __forceinline__ void load_working_set_xt(const double *__restrict__ X
         gram_rows<8, 2>(Xt, n, p, k, sm, w, pr);
         store_gram_rows<8>(sm, w, pr);
     }
-    if (w > kMidW) gram_blocked(Xt, n, p, k, sm, w);
+    if (w > kMidW) gram_tiles(Xt, n, p, k, sm, w);
     for (int q = lane; q < w; q += kWave) sm.sww[q * LW + q] = 1.0;
     wave_sync();
 #pragma unroll
@@ -204,7 +261,7 @@ __device__ __forceinline__ void load_working_set_xt(const double *__restrict__ X
 constexpr int kDirectMax = 24;
 
 template <int LW>
-__device__ bool polish_direct(WaveSm<double, LW> &sm, ColState<double, LW> &st, double lambda0, double tol)
+__device__ __forceinline__ bool polish_direct(WaveSm<double, LW> &sm, ColState<double, LW> &st, double lambda0, double tol)
 {
     static_assert(ColState<double, LW>::NS == 1, "one coordinate per lane");
     const int lane = lane_id();

@@ -36,3 +36,18 @@ def test_working_set_sizes(ctx, prec, m):
     for got, want in ((r.B, ref["B"]), (r.sigma, ref["sigma"]), (r.Omega, ref["Omega"])):
         assert rel_err(got.cpu().numpy(), want) <= 1e-6
     assert r.stats["columns_noconv"] == 0
+
+
+# the double Gram matrix of the mixed form's polish: rows around its blocks of
+# 16 (m + 1 of them), samples around its steps of 32 and 16, odd and even
+@pytest.mark.parametrize("n", [41, 64, 250, 701])
+@pytest.mark.parametrize("m", [3, 7, 8, 14, 15, 16, 17, 30])
+def test_polish_gram_sizes(ctx, m, n):
+    rng = np.random.default_rng(100 * m + n)
+    X = rng.standard_normal((n, 50))
+    X[:, 7] = X[:, 20:20 + m].sum(1) + 0.5 * rng.standard_normal(n)
+    lam0 = 0.4 if n < 100 else 0.15
+    ref = oracle.spmesl(X, lam0, tol=1e-12, original_scale=True)
+    r = ctx.solve(torch.from_numpy(X).to("cuda:0"), lam0, tol=1e-10, precision="mixed")
+    for got, want in ((r.B, ref["B"]), (r.sigma, ref["sigma"]), (r.Omega, ref["Omega"])):
+        assert rel_err(got.cpu().numpy(), want) <= 1e-6
