@@ -228,6 +228,8 @@ __device__ int kkt_pass_v(const TS *__restrict__ S, int64_t p, int64_t jend, int
     // the block's when the pass is shared)
     int *const plist = cp ? cp->pend[part] : sm.pend;
     int *const blist = cp ? cp->band[part] : band_idx + k * kBandMax;
+    // (lanes past jend read the row's first group, to no effect: a load under
+    // a condition would wait for itself, and the loads of a step go together)
     const int64_t nit = (jend + STEP - 1) / STEP;
     const int64_t it0 = part * nit / nparts, it1 = (part + 1) * nit / nparts;
     for (int64_t base = it0 * STEP; base < it1 * STEP; base += STEP) {
@@ -236,12 +238,7 @@ __device__ int kkt_pass_v(const TS *__restrict__ S, int64_t p, int64_t jend, int
         for (int c = 0; c < CH; ++c) {
             const int64_t j = base + (int64_t)(c * kWave + lane) * V;
             TS x[V];
-            if (j < jend) {
-                load_group<TS, V>(Sk + j, x);
-            } else {
-#pragma unroll
-                for (int e = 0; e < V; ++e) x[e] = TS(0);
-            }
+            load_group<TS, V>(Sk + (j < jend ? j : 0), x);
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[c][e] = (T)x[e];
         }
@@ -262,12 +259,7 @@ __device__ int kkt_pass_v(const TS *__restrict__ S, int64_t p, int64_t jend, int
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     const int64_t j = base + (int64_t)(c * kWave + lane) * V;
-                    if (j < jend) {
-                        load_group<TS, V>(rows[u] + j, x[u][c]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < V; ++e) x[u][c][e] = TS(0);
-                    }
+                    load_group<TS, V>(rows[u] + (j < jend ? j : 0), x[u][c]);
                 }
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -556,7 +548,7 @@ constexpr int kDirectSweeps = 12;
 // start, confirms the conditions on all of W (or moves on from it), so the
 // minimiser reached is the one of Algorithm 1.
 template <typename T, int LW>
-__device__ bool direct_fixed_point(ColState<T, LW> &st, unsigned *rlo, unsigned *rhi, T lambda0)
+__device__ __forceinline__ bool direct_fixed_point(ColState<T, LW> &st, unsigned *rlo, unsigned *rhi, T lambda0)
 {
     static_assert(ColState<T, LW>::kRegRows && ColState<T, LW>::NS == 1, "register rows, one coordinate per lane");
     const int lane = lane_id();
