@@ -566,10 +566,10 @@ static int fork_output_fill(spmesl_ctx *ctx, const spmesl_result *res, int64_t p
 // The dense tier (dense.hip) for the columns the 128-coordinate tier handed
 // over, reading S and writing the columns' results in place.
 template <typename T>
-static void enqueue_dense(const Plan &L, char *ws, Ctl *dctl, const ColArgs<T> &a, const Tune &tu, hipStream_t s,
-                          Marker *mk)
+static DenseJob<T, T> make_dense_job(const Plan &L, char *ws, Ctl *dctl, const ColArgs<T> &a, const Tune &tu)
 {
-    DenseArgs<T> d{};
+    DenseJob<T, T> j{};
+    DenseArgs<T> &d = j.a;
     d.S = a.S;
     d.Xt = nullptr;
     d.n = L.n;
@@ -606,7 +606,7 @@ static void enqueue_dense(const Plan &L, char *ws, Ctl *dctl, const ColArgs<T> &
     d.sk = (T *)(ws + L.dsk);
     d.counters = a.counters;
     d.flags = a.flags;
-    DenseSrc<T> src{};
+    DenseSrc<T> &src = j.src;
     src.cnt = a.w_cnt;
     src.idx = a.w_idx;
     src.beta = a.w_beta;
@@ -614,7 +614,15 @@ static void enqueue_dense(const Plan &L, char *ws, Ctl *dctl, const ColArgs<T> &
     src.sigma = a.sigma;
     src.pend_cnt = a.pend_cnt;
     src.pend_idx = a.pend_idx;
-    launch_dense<T, T>(d, src, s, L.sgroups);
+    return j;
+}
+
+template <typename T>
+static void enqueue_dense(const Plan &L, char *ws, Ctl *dctl, const ColArgs<T> &a, const Tune &tu, hipStream_t s,
+                          Marker *mk)
+{
+    const DenseJob<T, T> j = make_dense_job<T>(L, ws, dctl, a, tu);
+    launch_dense<T, T>(j.a, j.src, s, L.sgroups);
     mark(mk, s, "dense");
 }
 
@@ -754,16 +762,30 @@ static int enqueue_columns(const Plan &L, char *ws, Ctl *dctl, const spmesl_opti
 }
 
 // Column statistics and the standardised copies of X the form needs.
+static SplitJob make_split_job(const Plan &L, const spmesl_problem *prob, char *ws, Ctl *dctl)
+{
+    SplitJob j{};
+    j.X = prob->X;
+    j.n = prob->n;
+    j.p = prob->p;
+    j.ldx = prob->ldx;
+    j.mean = (double *)(ws + L.mean);
+    j.scale = (double *)(ws + L.scale);
+    j.Xt = (double *)(ws + L.xt);
+    j.split = L.data ? nullptr : (uint16_t *)(ws + L.split);
+    j.npad = L.npad;
+    j.flags = &dctl->flags;
+    j.zero_cnt = (int *)(ws + L.pendcnt);
+    return j;
+}
+
 static void enqueue_standardize(const Plan &L, const spmesl_problem *prob, char *ws, Ctl *dctl, hipStream_t s,
                                 Marker *mk)
 {
     const int64_t n = prob->n, p = prob->p;
     double *mean = (double *)(ws + L.mean);
     double *scale = (double *)(ws + L.scale);
-    if (L.prec == SPMESL_MIXED &&
-        launch_stats_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt),
-                           (uint16_t *)(ws + L.split), L.npad, &dctl->flags,
-                           (int *)(ws + L.pendcnt), s)) {
+    if (L.prec == SPMESL_MIXED && launch_stats_split(make_split_job(L, prob, ws, dctl), s)) {
         mark(mk, s, "standardize");
         return;
     }
@@ -855,10 +877,11 @@ static PolishArgs make_polish_args(const Plan &L, char *ws, Ctl *dctl, const spm
 // The columns whose double working sets outgrow the polish's: the dense
 // tier in double, from the float solution, with S[V, V] and the gradients
 // taken from the standardised data.
-static void enqueue_dense64(const PolishArgs &q, const Plan &L, char *ws, Ctl *dctl, const spmesl_options *opt,
-                            const Tune &tu, hipStream_t s, Marker *mk)
+static DenseJob<double, float> make_dense64_job(const PolishArgs &q, const Plan &L, char *ws, Ctl *dctl,
+                                                const spmesl_options *opt, const Tune &tu)
 {
-    DenseArgs<double> d{};
+    DenseJob<double, float> j{};
+    DenseArgs<double> &d = j.a;
     d.S = nullptr;
     d.Xt = q.Xt;
     d.n = L.n;
@@ -898,7 +921,7 @@ static void enqueue_dense64(const PolishArgs &q, const Plan &L, char *ws, Ctl *d
     d.E = (double *)(ws + L.de);
     d.counters = dctl->counters;
     d.flags = &dctl->flags;
-    DenseSrc<float> src{};
+    DenseSrc<float> &src = j.src;
     src.cnt = q.w_cnt32;
     src.idx = q.w_idx32;
     src.beta = q.w_beta32;
@@ -906,40 +929,61 @@ static void enqueue_dense64(const PolishArgs &q, const Plan &L, char *ws, Ctl *d
     src.sigma = q.sigma32;
     src.pend_cnt = (const int *)(ws + L.pendcnt);
     src.pend_idx = (const int *)(ws + L.pendidx);
-    launch_dense<double, float>(d, src, s, L.sgroups);
+    return j;
+}
+
+static void enqueue_dense64(const PolishArgs &q, const Plan &L, char *ws, Ctl *dctl, const spmesl_options *opt,
+                            const Tune &tu, hipStream_t s, Marker *mk)
+{
+    const DenseJob<double, float> j = make_dense64_job(q, L, ws, dctl, opt, tu);
+    launch_dense<double, float>(j.a, j.src, s, L.sgroups);
     mark(mk, s, "dense_polish");
 }
 
 // The statistics reduction of one problem (reads only the column results).
-static void enqueue_reduce_stats(const Plan &L, char *ws, Ctl *dctl, hipStream_t s)
+static StatsJob make_stats_job(const Plan &L, char *ws, Ctl *dctl)
 {
     const bool mixed = L.prec == SPMESL_MIXED;
-    launch_reduce_stats(L.p, (const int *)(ws + L.colinfo), mixed ? (const int *)(ws + L.polinfo) : nullptr,
-                        (const int *)(ws + (mixed ? L.wcnt64 : L.wcnt)),
-                        (const int *)(ws + (mixed ? L.cstat64 : L.cstat)), dctl->counters, &dctl->status1, s);
+    StatsJob j{};
+    j.p = L.p;
+    j.colinfo = (const int *)(ws + L.colinfo);
+    j.polinfo = mixed ? (const int *)(ws + L.polinfo) : nullptr;
+    j.w_cnt = (const int *)(ws + (mixed ? L.wcnt64 : L.wcnt));
+    j.col_status = (const int *)(ws + (mixed ? L.cstat64 : L.cstat));
+    j.counters = dctl->counters;
+    j.status_bits = &dctl->status1;
+    return j;
 }
 
-// B, sigma and Omega of one problem from its column results.
+// B, sigma and Omega of one problem from its column results (T: double, or
+// float in the float form).
+template <typename T>
+static ScatterJob<T> make_scatter_job(const Plan &L, char *ws, Ctl *dctl, const spmesl_result *res, int original)
+{
+    const bool mixed = L.prec == SPMESL_MIXED;
+    ScatterJob<T> j{};
+    j.p = L.p;
+    j.w_cnt = (const int *)(ws + (mixed ? L.wcnt64 : L.wcnt));
+    j.w_idx = (const int *)(ws + (mixed ? L.widx64 : L.widx));
+    j.w_beta = (const T *)(ws + (mixed ? L.wbeta64 : L.wbeta));
+    j.w_off = (const int *)(ws + (mixed ? L.woff64 : L.woff));
+    j.sigma = (const double *)(ws + (mixed ? L.sigma64 : L.sigma));
+    j.scale = (const double *)(ws + L.scale);
+    j.original = original;
+    j.B = res->B;
+    j.sig_out = res->sigma;
+    j.Omega = res->Omega;
+    j.flags = &dctl->flags;
+    return j;
+}
+
 static void enqueue_scatter(const Plan &L, char *ws, Ctl *dctl, const spmesl_result *res, int original,
                             hipStream_t s)
 {
-    const int64_t p = L.p;
-    const double *scale = (const double *)(ws + L.scale);
-    if (L.prec == SPMESL_FP64)
-        launch_scatter_outputs<double>(p, (const int *)(ws + L.wcnt), (const int *)(ws + L.widx),
-                                       (const double *)(ws + L.wbeta), (const int *)(ws + L.woff),
-                                       (const double *)(ws + L.sigma), scale, original, res->B, res->sigma,
-                                       res->Omega, &dctl->flags, s);
-    else if (L.prec == SPMESL_FP32)
-        launch_scatter_outputs<float>(p, (const int *)(ws + L.wcnt), (const int *)(ws + L.widx),
-                                      (const float *)(ws + L.wbeta), (const int *)(ws + L.woff),
-                                      (const double *)(ws + L.sigma), scale, original, res->B, res->sigma,
-                                      res->Omega, &dctl->flags, s);
+    if (L.prec == SPMESL_FP32)
+        launch_scatter_outputs(make_scatter_job<float>(L, ws, dctl, res, original), s);
     else
-        launch_scatter_outputs<double>(p, (const int *)(ws + L.wcnt64), (const int *)(ws + L.widx64),
-                                       (const double *)(ws + L.wbeta64), (const int *)(ws + L.woff64),
-                                       (const double *)(ws + L.sigma64), scale, original, res->B, res->sigma,
-                                       res->Omega, &dctl->flags, s);
+        launch_scatter_outputs(make_scatter_job<double>(L, ws, dctl, res, original), s);
 }
 
 // Enqueue one full solve.  ws: workspace base laid out by `L`; dctl: this
@@ -1039,7 +1083,7 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
         HIPTRY(ctx, hipEventRecord(ctx->fork2, s));
         HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2, 0));
         mark(mk, ctx->side, nullptr);
-        enqueue_reduce_stats(L, ws, dctl, ctx->side);
+        launch_reduce_stats(make_stats_job(L, ws, dctl), ctx->side);
         mark(mk, ctx->side, "reduce_stats");
         HIPTRY(ctx, hipEventRecord(ctx->join2, ctx->side));
     }
@@ -1079,8 +1123,7 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
     mark(mk, s, nullptr);
     launch_zero_words((uint32_t *)dctl, sizeof(Ctl) / 4, s);
     mark(mk, s, "zero_control");
-    if (!launch_stats_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt), nullptr, L.npad,
-                            &dctl->flags, (int *)(ws + L.pendcnt), s)) {
+    if (!launch_stats_split(make_split_job(L, prob, ws, dctl), s)) {
         launch_colstats(prob->X, n, p, prob->ldx, (double *)(ws + L.partial), L.rchunks, mean, scale,
                         &dctl->flags, (int *)(ws + L.pendcnt), s);
         launch_standardize_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt), nullptr, L.npad, s);
@@ -1154,17 +1197,13 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
     HIPTRY(ctx, hipEventRecord(ctx->fork2, s));
     HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2, 0));
     mark(mk, ctx->side, nullptr);
-    launch_reduce_stats(p, (const int *)(ws + L.colinfo), nullptr, (const int *)(ws + L.wcnt),
-                        (const int *)(ws + L.cstat), dctl->counters, &dctl->status1, ctx->side);
+    launch_reduce_stats(make_stats_job(L, ws, dctl), ctx->side);
     mark(mk, ctx->side, "reduce_stats");
     HIPTRY(ctx, hipEventRecord(ctx->join2, ctx->side));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[4], s));
     if (res->B || res->Omega) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
     mark(mk, s, "wait_fill");
-    launch_scatter_outputs<double>(p, (const int *)(ws + L.wcnt), (const int *)(ws + L.widx),
-                                   (const double *)(ws + L.wbeta), (const int *)(ws + L.woff),
-                                   (const double *)(ws + L.sigma), scale, original, res->B, res->sigma, res->Omega,
-                                   &dctl->flags, s);
+    enqueue_scatter(L, ws, dctl, res, original, s);
     mark(mk, s, "scatter");
     HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join2, 0));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[5], s));
@@ -1181,8 +1220,7 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
 // never captures or instantiates a graph; measured on a cycle of six calls
 // over fresh output memory (n = 250, p = 500, mixed) each call took 0.52 ms
 // where every one of them was captured, and takes 0.29 ms with this rule; the
-// first call on new memory 0.42 and 0.36 ms.  capture_first: captured on
-// first sight (a batch's many launches).
+// first call on new memory 0.42 and 0.36 ms.
 // A graph lives as long as its context: destroying one that had been
 // replayed many times without a wait, after its stream had been
 // synchronised, ended in a segmentation fault on the host.  A context that
@@ -1190,7 +1228,7 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
 // Kernel launches, event records and waits are the only stream work `body`
 // does (no memset or copy nodes).
 template <typename F>
-static int run_graph(spmesl_ctx *ctx, std::vector<unsigned char> &&key, F &&body, bool capture_first = false)
+static int run_graph(spmesl_ctx *ctx, std::vector<unsigned char> &&key, F &&body)
 {
     hipStream_t user = ctx->stream;
     for (auto &cg : ctx->graphs)
@@ -1202,14 +1240,11 @@ static int run_graph(spmesl_ctx *ctx, std::vector<unsigned char> &&key, F &&body
     auto &seen = ctx->seen;
     const auto it = std::find(seen.begin(), seen.end(), key);
     if (it == seen.end()) {
-        if (!capture_first) {
-            if (seen.size() >= spmesl_ctx::kMaxSeen) seen.pop_back();
-            seen.insert(seen.begin(), std::move(key));
-            return body();
-        }
-    } else {
-        seen.erase(it);
+        if (seen.size() >= spmesl_ctx::kMaxSeen) seen.pop_back();
+        seen.insert(seen.begin(), std::move(key));
+        return body();
     }
+    seen.erase(it);
     if (!ctx->cap) HIPTRY(ctx, hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking));
     HIPTRY(ctx, hipStreamBeginCapture(ctx->cap, hipStreamCaptureModeThreadLocal));
     ctx->stream = ctx->cap;
@@ -1263,18 +1298,21 @@ static int decode(const Ctl &c, int64_t p, spmesl_stats *st)
 
 
 // ---------------------------------------------------------------------------
-// The grouped batch (mixed form).  Every step of the path runs once for all
-// problems: the covariance tiles, the first solves, the row-tiled KKT pass,
-// the re-solves, the escalations and the polish each take one launch whose
+// The grouped batch.  Every step of the path runs once for all problems: the
+// fused standardisation, the output fills, the covariance tiles, the first
+// solves, the row-tiled KKT pass, the re-solves, the escalations, the polish,
+// the dense tier, the statistics and the scatter each take one launch whose
 // work items span the problems (a table of per-problem arguments, and the
 // offsets of each problem's items), so that small problems and the slow
 // columns of each fill the chip together instead of one problem's tail at a
-// time.  Each problem keeps its own workspace region and control block; a
+// time (16 hub networks with the standardisation, fills, dense tier,
+// statistics and scatter per problem, 4-12 us a launch: 1.16 ms; now 0.88).  Each problem keeps its own workspace region and control block; a
 // column's arithmetic is that of the single solve.
 // ---------------------------------------------------------------------------
 struct BatchTabs {
     // uploaded from the host: the tables and the host-known offsets
-    size_t first, resume, wide, kkt, polish, syrk, col_off, tile_off, kkt_off, upload;
+    size_t split, first, resume, wide, kkt, polish, syrk, dense, stats, scatter, fill;
+    size_t split8_off, split4_off, col_off, tile_off, kkt_off, dense_off, scatter_off, upload;
     // written on the device: offsets of the device-counted lists
     size_t dirty_off, esc_off, escp_off;
     size_t bytes;
@@ -1288,6 +1326,13 @@ static BatchTabs batch_tabs(int count)
     const size_t col = std::max(sizeof(ColArgs<float>), sizeof(ColArgs<double>));
     const size_t kkt = std::max(sizeof(KktJob<float>), sizeof(KktJob<double>));
     const size_t syrk = std::max({sizeof(SyrkJob), sizeof(SyrkJobT<float>), sizeof(SyrkJobT<double>)});
+    const size_t dense = std::max({sizeof(DenseJob<float, float>), sizeof(DenseJob<double, double>),
+                                   sizeof(DenseJob<double, float>)});
+    t.split = b.take(c * sizeof(SplitJob));
+    t.dense = b.take(c * dense);
+    t.stats = b.take(c * sizeof(StatsJob));
+    t.scatter = b.take(c * std::max(sizeof(ScatterJob<float>), sizeof(ScatterJob<double>)));
+    t.fill = b.take(2 * c * sizeof(FillJob));
     t.first = b.take(c * col);
     t.resume = b.take(c * col);
     t.wide = b.take(c * col);
@@ -1297,6 +1342,10 @@ static BatchTabs batch_tabs(int count)
     t.col_off = b.take(offs);
     t.tile_off = b.take(offs);
     t.kkt_off = b.take(offs);
+    t.split8_off = b.take(offs);
+    t.split4_off = b.take(offs);
+    t.dense_off = b.take(offs);
+    t.scatter_off = b.take(offs);
     t.upload = b.cur;
     t.dirty_off = b.take(offs);
     t.esc_off = b.take(offs);
@@ -1357,22 +1406,27 @@ static int ensure_stage(spmesl_ctx *ctx, size_t bytes)
     return SPMESL_OK;
 }
 
-// Fill the zero of the dense outputs of every problem on the second stream
-// (`which` as in fork_output_fill).
-static int fork_batch_fill(spmesl_ctx *ctx, int count, const spmesl_result *res, const std::vector<Plan> &plans,
-                           hipStream_t s, int which)
+// The outputs that the zero fill of mask `which` (as in fork_output_fill)
+// clears: B's before Omega's.
+static std::vector<FillJob> batch_fill_jobs(int count, const spmesl_result *res, const std::vector<Plan> &plans,
+                                            int which)
 {
-    const int fb = resolve_tune(ctx->tune).fill_blocks;
-    bool any = false;
-    for (int i = 0; i < count; ++i) any = any || ((which & 1) && res[i].B) || ((which & 2) && res[i].Omega);
-    if (!any) return SPMESL_OK;
+    std::vector<FillJob> j;
+    for (int m = 1; m <= 2; m <<= 1)
+        for (int i = 0; i < count && (which & m); ++i) {
+            double *A = m == 1 ? res[i].B : res[i].Omega;
+            if (A) j.push_back(FillJob{A, plans[(size_t)i].p * plans[(size_t)i].p});
+        }
+    return j;
+}
+
+// Clear fill jobs [j0, j1) of the batch's table on the second stream.
+static int fork_batch_fill(spmesl_ctx *ctx, const FillJob *tab, int j0, int j1, hipStream_t s)
+{
+    if (j0 >= j1) return SPMESL_OK;
     HIPTRY(ctx, hipEventRecord(ctx->fork, s));
     HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork, 0));
-    for (int i = 0; i < count; ++i) {
-        const int64_t p = plans[(size_t)i].p;
-        if ((which & 1) && res[i].B) launch_fill_zero(res[i].B, p * p, ctx->side, fb);
-        if ((which & 2) && res[i].Omega) launch_fill_zero(res[i].Omega, p * p, ctx->side, fb);
-    }
+    launch_fill_zero_grouped(tab + j0, j1 - j0, ctx->side, resolve_tune(ctx->tune).fill_blocks);
     HIPTRY(ctx, hipEventRecord(ctx->join, ctx->side));
     return SPMESL_OK;
 }
@@ -1381,6 +1435,9 @@ static int fork_batch_fill(spmesl_ctx *ctx, int count, const spmesl_result *res,
 // Returns the grid sizes the launches need.
 struct BatchGrids {
     int64_t cols = 0, tiles = 0, kkt_blocks = 0, pmax = 0;
+    int64_t split8 = 0, split4 = 0, nmax8 = 0, nmax4 = 0;  // fused standardisations of either width: blocks, most samples
+    int64_t dense = 0, scatter = 0;
+    int fill_early = 0, fills = 0;  // fill jobs ahead of the covariance, and all
     int rj = 4;
     int syrk_edge = 64;  // covariance tile edge
 };
@@ -1409,7 +1466,8 @@ static ColArgs<T> batch_col_args(const Plan &L, char *ws, Ctl *c, const spmesl_o
 }
 
 template <typename T>
-static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_options *opts,
+static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_problem *probs,
+                                     const spmesl_options *opts, const spmesl_result *res,
                                      const std::vector<Plan> &plans, const BatchLayout &B, unsigned char *h)
 {
     const Tune tu = resolve_tune(ctx->tune);
@@ -1440,7 +1498,19 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_op
     auto *col_off = (int64_t *)(h + t.col_off);
     auto *tile_off = (int64_t *)(h + t.tile_off);
     auto *kkt_off = (int64_t *)(h + t.kkt_off);
-    col_off[0] = tile_off[0] = kkt_off[0] = 0;
+    auto *split8_off = (int64_t *)(h + t.split8_off);
+    auto *split4_off = (int64_t *)(h + t.split4_off);
+    auto *dense_off = (int64_t *)(h + t.dense_off);
+    auto *scatter_off = (int64_t *)(h + t.scatter_off);
+    col_off[0] = tile_off[0] = kkt_off[0] = split8_off[0] = split4_off[0] = dense_off[0] = scatter_off[0] = 0;
+    // the order of fork_output_fill: what the launch shape clears early first
+    const int early = tu.fill_split == 0 ? 3 : (tu.fill_split == 1 ? 1 : 0);
+    for (const int which : {early, 3 & ~early}) {
+        const std::vector<FillJob> j = batch_fill_jobs(count, res, plans, which);
+        std::copy(j.begin(), j.end(), (FillJob *)(h + t.fill) + gr.fills);
+        gr.fills += (int)j.size();
+        if (which == early) gr.fill_early = gr.fills;
+    }
     for (int i = 0; i < count; ++i) {
         const Plan &L = plans[(size_t)i];
         const spmesl_options *opt = &opts[i];
@@ -1470,7 +1540,24 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_op
             int mo, ms, mr;
             limits_of(opt, &mo, &ms, &mr);
             pol[i] = make_polish_args(L, ws, c, opt, mo, ms, mr);
+            ((DenseJob<double, float> *)(h + t.dense))[i] = make_dense64_job(pol[i], L, ws, c, opt, tu);
+        } else {
+            ((DenseJob<T, T> *)(h + t.dense))[i] = make_dense_job<T>(L, ws, c, batch_col_args<T>(L, ws, c, opt), tu);
         }
+        dense_off[i + 1] = dense_off[i] + L.sgroups;
+        ((SplitJob *)(h + t.split))[i] = make_split_job(L, &probs[i], ws, c);
+        const int sw = L.prec == SPMESL_MIXED ? stats_split_width(L.n) : 0;
+        split8_off[i + 1] = split8_off[i] + (sw == 8 ? (L.p + 7) / 8 : 0);
+        split4_off[i + 1] = split4_off[i] + (sw == 4 ? (L.p + 3) / 4 : 0);
+        if (sw == 8) gr.nmax8 = std::max(gr.nmax8, L.n);
+        if (sw == 4) gr.nmax4 = std::max(gr.nmax4, L.n);
+        ((StatsJob *)(h + t.stats))[i] = make_stats_job(L, ws, c);
+        const int original = opt->output_scale == SPMESL_SCALE_ORIGINAL;
+        if (L.prec == SPMESL_FP32)
+            ((ScatterJob<float> *)(h + t.scatter))[i] = make_scatter_job<float>(L, ws, c, &res[i], original);
+        else
+            ((ScatterJob<double> *)(h + t.scatter))[i] = make_scatter_job<double>(L, ws, c, &res[i], original);
+        scatter_off[i + 1] = scatter_off[i] + scatter_blocks(L.p);
         col_off[i + 1] = col_off[i] + L.p;
         tile_off[i + 1] = tile_off[i] + tiles;
         kkt_off[i + 1] = kkt_off[i] + blocks;
@@ -1479,6 +1566,10 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_op
     gr.cols = col_off[count];
     gr.tiles = tile_off[count];
     gr.kkt_blocks = kkt_off[count];
+    gr.split8 = split8_off[count];
+    gr.split4 = split4_off[count];
+    gr.dense = dense_off[count];
+    gr.scatter = scatter_off[count];
     return gr;
 }
 
@@ -1488,13 +1579,13 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
                                  const BatchLayout &B, const BatchGrids &gr)
 {
     hipStream_t s = ctx->stream;
-    const Tune tu = resolve_tune(ctx->tune);
     const bool mixed = plans[0].prec == SPMESL_MIXED;
     char *ws0 = ctx->ws;
     Ctl *dctl = (Ctl *)(ws0 + B.ctl_off);
     const unsigned char *tb = (const unsigned char *)(ws0 + B.tab_off);
     const BatchTabs &t = B.t;
     const auto *col_off = (const int64_t *)(tb + t.col_off);
+    const auto *dense_off = (const int64_t *)(tb + t.dense_off);
     auto *dirty_off = (int64_t *)(tb + t.dirty_off);
     auto *esc_off = (int64_t *)(tb + t.esc_off);
     auto *escp_off = (int64_t *)(tb + t.escp_off);
@@ -1502,10 +1593,16 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     auto wsi = [&](int i) { return ws0 + B.ws_off[(size_t)i]; };
 
     launch_zero_words((uint32_t *)dctl, (int64_t)count * (int64_t)(sizeof(Ctl) / 4), s);
-    for (int i = 0; i < count; ++i) enqueue_standardize(plans[(size_t)i], &probs[i], wsi(i), dctl + i, s, nullptr);
-    const int early = tu.fill_split == 0 ? 3 : (tu.fill_split == 1 ? 1 : 0);
-    const int late = 3 & ~early;
-    int v = early ? fork_batch_fill(ctx, count, res, plans, s, early) : (int)SPMESL_OK;
+    // one launch for each width of the fused standardisation; a problem it
+    // does not apply to takes its own launches
+    const auto *split = (const SplitJob *)(tb + t.split);
+    launch_stats_split_grouped(split, (const int64_t *)(tb + t.split8_off), count, gr.split8, gr.nmax8, 8, s);
+    launch_stats_split_grouped(split, (const int64_t *)(tb + t.split4_off), count, gr.split4, gr.nmax4, 4, s);
+    for (int i = 0; i < count; ++i)
+        if (!mixed || stats_split_width(plans[(size_t)i].n) == 0)
+            enqueue_standardize(plans[(size_t)i], &probs[i], wsi(i), dctl + i, s, nullptr);
+    const auto *fill = (const FillJob *)(tb + t.fill);
+    int v = fork_batch_fill(ctx, fill, 0, gr.fill_early, s);
     if (v != SPMESL_OK) return v;
     if (mixed)
         launch_syrk_bf16x3_grouped((const SyrkJob *)(tb + t.syrk), (const int64_t *)(tb + t.tile_off), count,
@@ -1516,7 +1613,7 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     launch_colsolve_first_grouped<T>((const ColArgs<T> *)(tb + t.first), col_off, count, gr.cols, s);
     launch_kkt_rows_grouped<T>((const KktJob<T> *)(tb + t.kkt), (const int64_t *)(tb + t.kkt_off), count,
                                gr.kkt_blocks, gr.rj, gr.pmax, s);
-    if (late && (v = fork_batch_fill(ctx, count, res, plans, s, late)) != SPMESL_OK) return v;
+    if ((v = fork_batch_fill(ctx, fill, gr.fill_early, gr.fills, s)) != SPMESL_OK) return v;
     // re-solves of the flagged columns, then every escalated column (the
     // first solves' and the re-solves') in the wide tier
     launch_group_offsets(&dctl->dirty, ctl_words, count, dirty_off, s);
@@ -1525,33 +1622,25 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     launch_colsolve_list_grouped<T>((const ColArgs<T> *)(tb + t.wide), esc_off, count, 1, s);
     if (mixed) {
         // the double polish of every column, then its escalations, then the
-        // double dense tier of each problem
+        // double dense tier
         const PolishArgs *ptab = (const PolishArgs *)(tb + t.polish);
         launch_polish_grouped(ptab, col_off, count, gr.cols, 0, s);
         launch_group_offsets(&dctl->esc_polish, ctl_words, count, escp_off, s);
         launch_polish_grouped(ptab, escp_off, count, gr.cols, 1, s);
-        for (int i = 0; i < count; ++i) {
-            int mo, ms, mr;
-            limits_of(&opts[i], &mo, &ms, &mr);
-            const PolishArgs q = make_polish_args(plans[(size_t)i], wsi(i), dctl + i, &opts[i], mo, ms, mr);
-            enqueue_dense64(q, plans[(size_t)i], wsi(i), dctl + i, &opts[i], tu, s, nullptr);
-        }
+        launch_dense_grouped((const DenseJob<double, float> *)(tb + t.dense), dense_off, count, gr.dense, s);
     } else {
-        // the dense tier of each problem
-        for (int i = 0; i < count; ++i)
-            enqueue_dense<T>(plans[(size_t)i], wsi(i), dctl + i,
-                             batch_col_args<T>(plans[(size_t)i], wsi(i), dctl + i, &opts[i]), tu, s, nullptr);
+        launch_dense_grouped((const DenseJob<T, T> *)(tb + t.dense), dense_off, count, gr.dense, s);
     }
     HIPTRY(ctx, hipEventRecord(ctx->fork2, s));
     HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2, 0));
-    for (int i = 0; i < count; ++i) enqueue_reduce_stats(plans[(size_t)i], wsi(i), dctl + i, ctx->side);
+    launch_reduce_stats_grouped((const StatsJob *)(tb + t.stats), count, ctx->side);
     HIPTRY(ctx, hipEventRecord(ctx->join2, ctx->side));
-    bool fill = false;
-    for (int i = 0; i < count; ++i) fill = fill || res[i].B || res[i].Omega;
-    if (fill) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
-    for (int i = 0; i < count; ++i)
-        enqueue_scatter(plans[(size_t)i], wsi(i), dctl + i, &res[i], opts[i].output_scale == SPMESL_SCALE_ORIGINAL,
-                        s);
+    if (gr.fills) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
+    const auto *scatter_off = (const int64_t *)(tb + t.scatter_off);
+    if (plans[0].prec == SPMESL_FP32)
+        launch_scatter_grouped((const ScatterJob<float> *)(tb + t.scatter), scatter_off, count, gr.scatter, s);
+    else
+        launch_scatter_grouped((const ScatterJob<double> *)(tb + t.scatter), scatter_off, count, gr.scatter, s);
     HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join2, 0));
     HIPTRY(ctx, hipGetLastError());
     return SPMESL_OK;
@@ -1570,8 +1659,8 @@ static int solve_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_problem 
     // the tables hold workspace addresses: built for this workspace, and
     // uploaded ahead of the solves (outside any graph)
     const bool dbl = plans[0].prec == SPMESL_FP64;
-    const BatchGrids gr = dbl ? build_batch_tables<double>(ctx, count, opts.data(), plans, B, ctx->stage)
-                              : build_batch_tables<float>(ctx, count, opts.data(), plans, B, ctx->stage);
+    const BatchGrids gr = dbl ? build_batch_tables<double>(ctx, count, probs, opts.data(), res, plans, B, ctx->stage)
+                              : build_batch_tables<float>(ctx, count, probs, opts.data(), res, plans, B, ctx->stage);
     HIPTRY(ctx, hipMemcpyAsync(ctx->ws + B.tab_off, ctx->stage, B.t.upload, hipMemcpyHostToDevice, ctx->stream));
     const spmesl_options *opt = &opts[0];
     auto body = [&] {
@@ -1590,7 +1679,7 @@ static int solve_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_problem 
             key_problem(k, probs[i], res[i]);
             key_options(k, opts[(size_t)i]);
         }
-        v = run_graph(ctx, std::move(k.b), body, true);
+        v = run_graph(ctx, std::move(k.b), body);
     }
     if (v != SPMESL_OK) return v;
     Ctl *dctl = (Ctl *)(ctx->ws + B.ctl_off);
@@ -2034,7 +2123,7 @@ int spmesl_solve_batch(spmesl_ctx *ctx, int count, const spmesl_problem *probs,
             key_options(k, opts[(size_t)i]);
             key_tuning(k, ctx->tune);
         }
-        v = run_graph(ctx, std::move(k.b), body, true);
+        v = run_graph(ctx, std::move(k.b), body);
     }
     if (v != SPMESL_OK) return v;
     HIPTRY(ctx, hipMemcpyAsync(ctx->pinned, dctl, (size_t)count * sizeof(Ctl),
@@ -2187,8 +2276,12 @@ int spmesl_scaled_lasso(spmesl_ctx *ctx, const spmesl_problem *prob, const doubl
     v = enqueue_columns<double>(L, ws, dctl, opt, tu, opt->tol, 0.0, max_outer, max_sweeps, max_rounds, s,
                                 nullptr, [] { return (int)SPMESL_OK; }, px);
     if (v != SPMESL_OK) return v;
-    launch_reduce_stats(m, (const int *)(ws + L.colinfo) + 4 * px, nullptr, (const int *)(ws + L.wcnt) + px,
-                        (const int *)(ws + L.cstat) + px, dctl->counters, &dctl->status1, s);
+    StatsJob sj = make_stats_job(L, ws, dctl);  // of the responses' columns
+    sj.p = m;
+    sj.colinfo += 4 * px;
+    sj.w_cnt += px;
+    sj.col_status += px;
+    launch_reduce_stats(sj, s);
     launch_fill_zero(beta, px * m, s);
     launch_scatter_lasso<double>(px, m, (const int *)(ws + L.wcnt), (const int *)(ws + L.widx),
                                  (const double *)(ws + L.wbeta), (const int *)(ws + L.woff),

@@ -177,9 +177,20 @@ inline int64_t split_size(int64_t p, int64_t npad) { return (p + 15) / 16 * 16 *
 // Mixed form: column statistics and the split in one kernel (X read once).
 // Returns false (nothing launched) when a strip of n samples does not fit
 // the kernel's LDS budget; the caller then takes the two-kernel path.
-bool launch_stats_split(const double *X, int64_t n, int64_t p, int64_t ldx, double *mean,
-                        double *scale, double *Xt, uint16_t *split, int64_t npad,
-                        int *flags, int *zero_cnt, hipStream_t s);
+struct SplitJob {
+    const double *X;
+    int64_t n, p, ldx;
+    double *mean, *scale, *Xt;
+    uint16_t *split;  // null: not written
+    int64_t npad;
+    int *flags, *zero_cnt;
+};
+bool launch_stats_split(const SplitJob &j, hipStream_t s);
+// Variables per block of that kernel (8 or 4; 0: it does not apply).
+int stats_split_width(int64_t n);
+// ... for many problems of one width (the blocks of problem d are off[d] ..).
+void launch_stats_split_grouped(const SplitJob *tab, const int64_t *off, int nd, int64_t blocks, int64_t nmax, int sw,
+                                hipStream_t s);
 void launch_standardize_split(const double *X, int64_t n, int64_t p, int64_t ldx,
                               const double *mean, const double *scale, double *Xt,
                               uint16_t *split, int64_t npad, hipStream_t s);
@@ -358,6 +369,14 @@ struct DenseArgs {
 };
 template <typename T, typename TS>
 void launch_dense(const DenseArgs<T> &a, const DenseSrc<TS> &src, hipStream_t s, int blocks = 1);
+// Many problems' queues in one launch (the workgroups of problem d are off[d] ..).
+template <typename T, typename TS>
+struct DenseJob {
+    DenseArgs<T> a;
+    DenseSrc<TS> src;
+};
+template <typename T, typename TS>
+void launch_dense_grouped(const DenseJob<T, TS> *tab, const int64_t *off, int nd, int64_t blocks, hipStream_t s);
 
 // Warm start of the column solves from a caller's B0 (p x p row-major,
 // column k = beta of response k) and sigma0 (p), on the standardised scale or
@@ -448,20 +467,41 @@ void launch_polish_grouped(const PolishArgs *tab, const int64_t *off, int nd, in
 // Reduce the per-column counters and final statuses of one solve into the
 // control block: counters[kNumCounters] and status bits (1 no convergence,
 // 2 degenerate, 4 working set overflow).
-void launch_reduce_stats(int64_t p, const int *colinfo, const int *polinfo, const int *w_cnt,
-                         const int *col_status, unsigned long long *counters, int *status_bits,
-                         hipStream_t s);
+struct StatsJob {
+    int64_t p;
+    const int *colinfo, *polinfo, *w_cnt, *col_status;
+    unsigned long long *counters;
+    int *status_bits;
+};
+void launch_reduce_stats(const StatsJob &j, hipStream_t s);
+void launch_reduce_stats_grouped(const StatsJob *tab, int nd, hipStream_t s);
 
 // Zero n 32-bit words (a kernel, so it is safe inside captured graphs).
 void launch_zero_words(uint32_t *a, int64_t n, hipStream_t s);
 
 // Outputs.
 void launch_fill_zero(double *A, int64_t count, hipStream_t s, int max_blocks = 64);
+struct FillJob {
+    double *A;
+    int64_t count;
+};
+void launch_fill_zero_grouped(const FillJob *tab, int nd, hipStream_t s, int max_blocks);
 template <typename T>
-void launch_scatter_outputs(int64_t p, const int *w_cnt, const int *w_idx, const T *w_beta, const int *w_off,
-                            const double *sigma, const double *scale, int original_scale,
-                            double *B, double *sig_out, double *Omega, const int *flags,
-                            hipStream_t s);
+struct ScatterJob {
+    int64_t p;
+    const int *w_cnt, *w_idx;
+    const T *w_beta;
+    const int *w_off;
+    const double *sigma, *scale;
+    int original;
+    double *B, *sig_out, *Omega;
+    const int *flags;
+};
+int64_t scatter_blocks(int64_t p);
+template <typename T>
+void launch_scatter_outputs(const ScatterJob<T> &j, hipStream_t s);
+template <typename T>
+void launch_scatter_grouped(const ScatterJob<T> *tab, const int64_t *off, int nd, int64_t blocks, hipStream_t s);
 void launch_symmetrize_dense(int64_t p, const double *Om1, double *Om, hipStream_t s);
 template <typename T>
 void launch_scatter_lasso(int64_t k0, int64_t m, const int *w_cnt, const int *w_idx, const T *w_beta,

@@ -51,6 +51,8 @@
 //   n = 400, p = 2500, data form (157 groups, V about 40): 6.0 -> 1.2 ms a
 //     solve: a group's iterations 450 -> 40 us, a full gradient 870 -> 290 us
 //     (its 2 GB of Xt reads a pass come from the caches at 4.4 TB/s).
+#include <type_traits>
+
 #include "colsolve_dev.hpp"
 
 namespace spmesl {
@@ -875,22 +877,21 @@ __device__ __forceinline__ void iterate(const DenseArgs<T> &A, DenseSm<T> &sm, i
     __syncthreads();
 }
 
+// Workgroup bi of nb takes the queue's groups bi, bi + nb, ..
 template <typename T, typename TS, bool DATA>
-__global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src)
+__device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const DenseSrc<TS> &src, DenseSm<T> &sm, T *lds,
+                                             int64_t bi, int64_t nb)
 {
-    __shared__ DenseSm<T> sm;
-    extern __shared__ __align__(16) unsigned char dense_lds[];
-    T *const lds = reinterpret_cast<T *>(dense_lds);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     if (*A0.flags) return;
     const int64_t p = A0.p;
     // the queue, or (no queue) the columns 0 .. ncols - 1
     const int q = A0.queue ? *A0.qcnt : (int)A0.ncols;
-    if (q <= 0 || (int64_t)blockIdx.x * kDW >= q) return;
+    if (q <= 0 || bi * kDW >= q) return;
     // this workgroup's slice of the workspace
     DenseArgs<T> A = A0;
     {
-        const int64_t bi = blockIdx.x, vc = A0.vcap;
+        const int64_t vc = A0.vcap;
         A.mark += bi * p;
         A.V += bi * vc;
         A.Vold += bi * vc;
@@ -908,7 +909,7 @@ __global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src
     for (int64_t j = tid; j < p; j += kDT) A.mark[j] = 0;
     __syncthreads();
     const int b = A.block <= 16 ? 16 : (A.block <= 32 ? 32 : kBMax);
-    for (int g0 = (int)blockIdx.x * kDW; g0 < q; g0 += (int)gridDim.x * kDW) {
+    for (int g0 = (int)bi * kDW; g0 < q; g0 += (int)nb * kDW) {
         const int m = q - g0 < kDW ? q - g0 : kDW;
         // --- the group's columns and their start --------------------------
         if (tid < kDW) {
@@ -1093,6 +1094,27 @@ __global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src
     }
 }
 
+template <typename T, typename TS, bool DATA>
+__global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src)
+{
+    __shared__ DenseSm<T> sm;
+    extern __shared__ __align__(16) unsigned char dense_lds[];
+    dense_groups<T, TS, DATA>(A0, src, sm, reinterpret_cast<T *>(dense_lds), blockIdx.x, gridDim.x);
+}
+
+// block b is workgroup b - off[d] of problem d
+template <typename T, typename TS, bool DATA>
+__global__ __launch_bounds__(kDT) void k_dense_grouped(const DenseJob<T, TS> *__restrict__ tab,
+                                                       const int64_t *__restrict__ off, int nd)
+{
+    __shared__ DenseSm<T> sm;
+    extern __shared__ __align__(16) unsigned char dense_lds[];
+    const int64_t b = blockIdx.x;
+    const int d = group_of(off, nd, b);
+    dense_groups<T, TS, DATA>(tab[d].a, tab[d].src, sm, reinterpret_cast<T *>(dense_lds), b - off[d],
+                              off[d + 1] - off[d]);
+}
+
 } // namespace
 
 template <typename T, typename TS>
@@ -1107,6 +1129,21 @@ void launch_dense(const DenseArgs<T> &a, const DenseSrc<TS> &src, hipStream_t s,
     hipLaunchKernelGGL((k_dense<T, TS, false>), dim3(blocks), dim3(kDT), dense_lds_bytes<T>(), s, a, src);
 }
 
+template <typename T, typename TS>
+void launch_dense_grouped(const DenseJob<T, TS> *tab, const int64_t *off, int nd, int64_t blocks, hipStream_t s)
+{
+    // (from the data: the mixed form's polish; from S: the other forms)
+    constexpr bool DATA = !std::is_same<T, TS>::value;
+    hipLaunchKernelGGL((k_dense_grouped<T, TS, DATA>), dim3((unsigned)blocks), dim3(kDT), dense_lds_bytes<T>(), s, tab,
+                       off, nd);
+}
+
+template void launch_dense_grouped<double, double>(const DenseJob<double, double> *, const int64_t *, int, int64_t,
+                                                   hipStream_t);
+template void launch_dense_grouped<float, float>(const DenseJob<float, float> *, const int64_t *, int, int64_t,
+                                                 hipStream_t);
+template void launch_dense_grouped<double, float>(const DenseJob<double, float> *, const int64_t *, int, int64_t,
+                                                  hipStream_t);
 template void launch_dense<double, double>(const DenseArgs<double> &, const DenseSrc<double> &, hipStream_t, int);
 template void launch_dense<float, float>(const DenseArgs<float> &, const DenseSrc<float> &, hipStream_t, int);
 template void launch_dense<double, float>(const DenseArgs<double> &, const DenseSrc<float> &, hipStream_t, int);

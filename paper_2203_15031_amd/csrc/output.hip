@@ -70,13 +70,12 @@ void launch_zero_words(uint32_t *a, int64_t n, hipStream_t s)
 // with every load of the pass in flight together (16-byte loads of the
 // counter records); sums are carried in double (exact below 2^53) through
 // DPP wave reductions, then one LDS step across the block's waves.
-__global__ __launch_bounds__(1024) void k_reduce_stats(int64_t p, const int *__restrict__ colinfo,
-                                                       const int *__restrict__ polinfo,
-                                                       const int *__restrict__ w_cnt,
-                                                       const int *__restrict__ col_status,
-                                                       unsigned long long *__restrict__ counters,
-                                                       int *__restrict__ status_bits)
+__device__ __forceinline__ void reduce_stats(const StatsJob &J)
 {
+    const int64_t p = J.p;
+    const int *__restrict__ colinfo = J.colinfo, *__restrict__ polinfo = J.polinfo, *__restrict__ w_cnt = J.w_cnt,
+                                *__restrict__ col_status = J.col_status;
+    unsigned long long *__restrict__ counters = J.counters;
     typedef int i4 __attribute__((ext_vector_type(4)));
     constexpr int U = 4;
     // outer, sweeps, updates, rounds, polish checks, polish added, noconv,
@@ -151,16 +150,26 @@ __global__ __launch_bounds__(1024) void k_reduce_stats(int64_t p, const int *__r
         counters[kCntSumW] = (unsigned long long)t[7];
         counters[kCntMaxW] = (unsigned long long)mw;
         counters[kCntMaxOuter] = (unsigned long long)mo;
-        *status_bits = bb;
+        *J.status_bits = bb;
     }
 }
 
-void launch_reduce_stats(int64_t p, const int *colinfo, const int *polinfo, const int *w_cnt,
-                         const int *col_status, unsigned long long *counters, int *status_bits,
-                         hipStream_t s)
+__global__ __launch_bounds__(1024) void k_reduce_stats(StatsJob J) { reduce_stats(J); }
+
+// (a block per problem)
+__global__ __launch_bounds__(1024) void k_reduce_stats_grouped(const StatsJob *__restrict__ tab)
 {
-    hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(1024), 0, s, p, colinfo, polinfo, w_cnt,
-                       col_status, counters, status_bits);
+    reduce_stats(tab[blockIdx.x]);
+}
+
+void launch_reduce_stats(const StatsJob &j, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(1024), 0, s, j);
+}
+
+void launch_reduce_stats_grouped(const StatsJob *tab, int nd, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_reduce_stats_grouped, dim3((unsigned)nd), dim3(1024), 0, s, tab);
 }
 
 __global__ __launch_bounds__(256) void k_fill_zero(double *__restrict__ A, int64_t count)
@@ -197,20 +206,44 @@ void launch_fill_zero(double *A, int64_t count, hipStream_t s, int max_blocks)
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, s, A, count);
 }
 
+// Many arrays in one launch, one after the other by the whole (small) grid.
+__global__ __launch_bounds__(256) void k_fill_zero_grouped(const FillJob *__restrict__ tab, int nd)
+{
+    typedef double dv2 __attribute__((ext_vector_type(2)));
+    const dv2 z = {0.0, 0.0};
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int d = 0; d < nd; ++d) {
+        double *A = tab[d].A;
+        int64_t count = tab[d].count;
+        if (((uintptr_t)A & 15u) != 0) {  // only 8-byte aligned: one element, then 16-byte groups
+            if (t0 == 0) *A = 0.0;
+            ++A;
+            --count;
+        }
+        dv2 *A2 = reinterpret_cast<dv2 *>(A);
+        for (int64_t i = t0; i < count / 2; i += stride) __builtin_nontemporal_store(z, &A2[i]);
+        if (t0 == 0 && (count & 1)) A[count - 1] = 0.0;
+    }
+}
+
+void launch_fill_zero_grouped(const FillJob *tab, int nd, hipStream_t s, int max_blocks)
+{
+    if (nd <= 0) return;
+    hipLaunchKernelGGL(k_fill_zero_grouped, dim3((unsigned)max_blocks), dim3(256), 0, s, tab, nd);
+}
+
 // one wave per column k; lanes walk the column's list
 template <typename T>
-__global__ __launch_bounds__(256) void k_scatter(int64_t p, const int *__restrict__ w_cnt,
-                                                 const int *__restrict__ w_idx,
-                                                 const T *__restrict__ w_beta,
-                                                 const int *__restrict__ w_off,
-                                                 const double *__restrict__ sigma,
-                                                 const double *__restrict__ scale, int original,
-                                                 double *__restrict__ B,
-                                                 double *__restrict__ sig_out,
-                                                 double *__restrict__ Om,
-                                                 const int *__restrict__ flags)
+__device__ __forceinline__ void scatter(const ScatterJob<T> &J, int64_t block)
 {
-    const int64_t k = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t p = J.p;
+    const int *__restrict__ w_cnt = J.w_cnt, *__restrict__ w_idx = J.w_idx, *__restrict__ w_off = J.w_off,
+                            *__restrict__ flags = J.flags;
+    const T *__restrict__ w_beta = J.w_beta;
+    const double *__restrict__ sigma = J.sigma, *__restrict__ scale = J.scale;
+    double *__restrict__ B = J.B, *__restrict__ sig_out = J.sig_out, *__restrict__ Om = J.Omega;
+    const int original = J.original;
+    const int64_t k = block * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (k >= p || *flags) return;
     int wk = w_cnt[k];
@@ -258,21 +291,40 @@ __global__ __launch_bounds__(256) void k_scatter(int64_t p, const int *__restric
 }
 
 template <typename T>
-void launch_scatter_outputs(int64_t p, const int *w_cnt, const int *w_idx, const T *w_beta, const int *w_off,
-                            const double *sigma, const double *scale, int original_scale,
-                            double *B, double *sig_out, double *Omega, const int *flags,
-                            hipStream_t s)
+__global__ __launch_bounds__(256) void k_scatter(ScatterJob<T> J)
 {
-    hipLaunchKernelGGL(k_scatter<T>, dim3((unsigned)((p + 3) / 4)), dim3(256), 0, s, p, w_cnt,
-                       w_idx, w_beta, w_off, sigma, scale, original_scale, B, sig_out, Omega, flags);
+    scatter(J, blockIdx.x);
 }
 
-template void launch_scatter_outputs<double>(int64_t, const int *, const int *, const double *, const int *,
-                                             const double *, const double *, int, double *,
-                                             double *, double *, const int *, hipStream_t);
-template void launch_scatter_outputs<float>(int64_t, const int *, const int *, const float *, const int *,
-                                            const double *, const double *, int, double *,
-                                            double *, double *, const int *, hipStream_t);
+// block b is block b - off[d] of problem d
+template <typename T>
+__global__ __launch_bounds__(256) void k_scatter_grouped(const ScatterJob<T> *__restrict__ tab,
+                                                         const int64_t *__restrict__ off, int nd)
+{
+    const int64_t b = blockIdx.x;
+    const int d = group_of(off, nd, b);
+    scatter(tab[d], b - off[d]);
+}
+
+int64_t scatter_blocks(int64_t p) { return (p + 3) / 4; }
+
+template <typename T>
+void launch_scatter_outputs(const ScatterJob<T> &j, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_scatter<T>, dim3((unsigned)scatter_blocks(j.p)), dim3(256), 0, s, j);
+}
+
+template <typename T>
+void launch_scatter_grouped(const ScatterJob<T> *tab, const int64_t *off, int nd, int64_t blocks, hipStream_t s)
+{
+    if (blocks <= 0) return;
+    hipLaunchKernelGGL(k_scatter_grouped<T>, dim3((unsigned)blocks), dim3(256), 0, s, tab, off, nd);
+}
+
+template void launch_scatter_outputs<double>(const ScatterJob<double> &, hipStream_t);
+template void launch_scatter_outputs<float>(const ScatterJob<float> &, hipStream_t);
+template void launch_scatter_grouped<double>(const ScatterJob<double> *, const int64_t *, int, int64_t, hipStream_t);
+template void launch_scatter_grouped<float>(const ScatterJob<float> *, const int64_t *, int, int64_t, hipStream_t);
 
 // The scaled lassos of the response columns k0 .. k0 + m - 1 (design columns
 // 0 .. k0 - 1), one wave per response r: beta (k0 x m row-major, zero-filled

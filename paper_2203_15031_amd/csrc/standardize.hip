@@ -223,21 +223,20 @@ __global__ __launch_bounds__(256) void k_standardize_split(
 // also zeroes the strip's screen counters (the covariance kernel appends to
 // them).
 template <int SW>
-__global__ __launch_bounds__(256) void k_stats_split(const double *__restrict__ X, int64_t n, int64_t p,
-                                                     int64_t ldx, double *__restrict__ mean,
-                                                     double *__restrict__ scale, double *__restrict__ Xt,
-                                                     uint16_t *__restrict__ split,
-                                                     int64_t npad, int *__restrict__ flags,
-                                                     int *__restrict__ zero_cnt)
+__device__ __forceinline__ void stats_split(const SplitJob &J, int64_t block, double *strip)  // strip: n x SWP
 {
+    const double *__restrict__ X = J.X;
+    const int64_t n = J.n, p = J.p, ldx = J.ldx, npad = J.npad;
+    double *__restrict__ mean = J.mean, *__restrict__ scale = J.scale, *__restrict__ Xt = J.Xt;
+    uint16_t *__restrict__ split = J.split;
+    int *__restrict__ flags = J.flags, *__restrict__ zero_cnt = J.zero_cnt;
     constexpr int SWP = SW + 1;         // odd row stride: by-variable reads hit distinct banks
     constexpr int G = 256 / SW;         // row groups
-    extern __shared__ double strip[];   // n x SWP
     __shared__ double part[G][SW];
     __shared__ double mv[SW], cv[SW];
     const int t = threadIdx.x;
     const int v = t % SW, g = t / SW;
-    const int64_t j0 = (int64_t)blockIdx.x * SW;
+    const int64_t j0 = block * SW;
     const int64_t j = j0 + v;
     for (int64_t i = g; i < n; i += G) strip[i * SWP + v] = j < p ? X[i * ldx + j] : 0.0;
     __syncthreads();
@@ -304,32 +303,56 @@ __global__ __launch_bounds__(256) void k_stats_split(const double *__restrict__ 
     }
 }
 
+template <int SW>
+__global__ __launch_bounds__(256) void k_stats_split(SplitJob J)
+{
+    extern __shared__ double strip[];
+    stats_split<SW>(J, blockIdx.x, strip);
+}
+
+// block b is block b - off[d] of problem d
+template <int SW>
+__global__ __launch_bounds__(256) void k_stats_split_grouped(const SplitJob *__restrict__ tab,
+                                                             const int64_t *__restrict__ off, int nd)
+{
+    extern __shared__ double strip[];
+    const int64_t b = blockIdx.x;
+    const int d = group_of(off, nd, b);
+    stats_split<SW>(tab[d], b - off[d], strip);
+}
+
 // Strip width for the fused kernel: 8 variables (64-byte row segments) when
 // the LDS strip fits 64 KB, else 4; 0 when neither does.  At n = 400,
 // p = 5000 the 8-wide strips (625 blocks, about five per CU) take 17 us where
 // 16-wide ones (313 blocks, two per CU) took 23 us and 4-wide ones 20 us.
-static int stats_split_width(int64_t n)
+int stats_split_width(int64_t n)
 {
     for (int sw = 8; sw >= 4; sw >>= 1)
         if ((size_t)n * (sw + 1) * 8 <= (size_t)64 * 1024) return sw;
     return 0;
 }
 
-bool launch_stats_split(const double *X, int64_t n, int64_t p, int64_t ldx, double *mean,
-                        double *scale, double *Xt, uint16_t *split, int64_t npad,
-                        int *flags, int *zero_cnt, hipStream_t s)
+static size_t stats_split_lds(int64_t n, int sw) { return (size_t)n * (sw + 1) * 8; }
+
+bool launch_stats_split(const SplitJob &j, hipStream_t s)
 {
-    const int sw = stats_split_width(n);
+    const int sw = stats_split_width(j.n);
     if (sw == 0) return false;
-    const size_t lds = (size_t)n * (sw + 1) * 8;
-    const unsigned blocks = (unsigned)((p + sw - 1) / sw);
-    if (sw == 8)
-        hipLaunchKernelGGL(k_stats_split<8>, dim3(blocks), dim3(256), lds, s, X, n, p, ldx, mean, scale,
-                           Xt, split, npad, flags, zero_cnt);
-    else
-        hipLaunchKernelGGL(k_stats_split<4>, dim3(blocks), dim3(256), lds, s, X, n, p, ldx, mean, scale,
-                           Xt, split, npad, flags, zero_cnt);
+    const dim3 blocks((unsigned)((j.p + sw - 1) / sw));
+    if (sw == 8) hipLaunchKernelGGL(k_stats_split<8>, blocks, dim3(256), stats_split_lds(j.n, 8), s, j);
+    else hipLaunchKernelGGL(k_stats_split<4>, blocks, dim3(256), stats_split_lds(j.n, 4), s, j);
     return true;
+}
+
+void launch_stats_split_grouped(const SplitJob *tab, const int64_t *off, int nd, int64_t blocks, int64_t nmax, int sw,
+                                hipStream_t s)
+{
+    if (blocks <= 0) return;
+    const size_t lds = stats_split_lds(nmax, sw);
+    if (sw == 8)
+        hipLaunchKernelGGL(k_stats_split_grouped<8>, dim3((unsigned)blocks), dim3(256), lds, s, tab, off, nd);
+    else
+        hipLaunchKernelGGL(k_stats_split_grouped<4>, dim3((unsigned)blocks), dim3(256), lds, s, tab, off, nd);
 }
 
 void launch_standardize_split(const double *X, int64_t n, int64_t p, int64_t ldx,
