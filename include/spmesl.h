@@ -286,9 +286,10 @@ typedef struct {
     int32_t screen_permille;  /* first working sets {j : |s_jk| > f lambda0 +
                                  tol}, f in thousandths (default 800) */
     int32_t fill_split;       /* where the zero fill of the dense outputs runs:
-                                 0 both beside the covariance kernel (default),
-                                 1 Omega's after the row-tiled KKT pass, 2 both
-                                 after it */
+                                 0 both beside the covariance kernel, 1 Omega's
+                                 after the row-tiled KKT pass, 2 both after it
+                                 (default, with every field 0: 2 in the float
+                                 and mixed forms from p = 1024, else 0) */
 } spmesl_tuning;
 
 /* Set (NULL: reset to the defaults) or read the context's launch shapes. */

@@ -68,7 +68,6 @@ struct Tune {
     int fill_blocks = kFillBlocks;
     int kkt_rows = 0;  // 0: the most that fit
     int screen_permille = kScreenPermille;
-    int fill_split = 0;
 };
 Tune resolve_tune(const spmesl_tuning &t)
 {
@@ -77,8 +76,24 @@ Tune resolve_tune(const spmesl_tuning &t)
     if (t.fill_blocks > 0) u.fill_blocks = t.fill_blocks;
     if (t.kkt_rows > 0) u.kkt_rows = t.kkt_rows;
     if (t.screen_permille > 0) u.screen_permille = t.screen_permille;
-    u.fill_split = t.fill_split;
     return u;
+}
+
+// ... and where the zero fill of `cells` output elements (per output) runs.
+// Shapes that were set decide it; with none set (every field 0) the double
+// form fills beside its covariance kernel, which leaves HBM idle (p = 5000:
+// 0.432 ms a solve against 0.438 with the fills after the KKT pass, p = 1000
+// 0.380 against 0.395), and so does a small problem, whose fill is short
+// (mixed, p = 200: 0.120 against 0.125).  The bf16 and float covariance
+// kernels write S as fast as the fill writes, and the latency-bound solves
+// after the KKT pass are the better company: mixed p = 5000 0.252 against
+// 0.270, p = 20000 4.70 against 5.29, 16 hub networks 0.804 against 0.834,
+// p = 2000 0.400 against 0.407 for two, float p = 2047 0.148 against 0.155.
+int fill_split_for(const spmesl_tuning &t, int prec, int64_t cells)
+{
+    const bool set = t.dense_block || t.fill_blocks || t.kkt_rows || t.screen_permille || t.fill_split;
+    if (set) return t.fill_split;
+    return prec != SPMESL_FP64 && cells >= (int64_t)1 << 20 ? 2 : 0;
 }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1012,17 +1027,10 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
     launch_zero_words((uint32_t *)dctl, sizeof(Ctl) / 4, s);
     mark(mk, s, "zero_control");
     enqueue_standardize(L, prob, ws, dctl, s, mk);
-    // The zero fill of the outputs goes on the second stream under the
-    // covariance kernel, which leaves HBM to it (double: MFMA-bound, 290 us at
-    // p = 5000; mixed: it slows that kernel from 86 to about 102 us), so that
-    // the latency-bound column solves after it run without the fill's 400 MB
-    // of writes beside them.  Measured at p = 5000, mixed: 0.262 ms per solve
-    // against 0.269 with the fill after the row-tiled KKT pass (which left the
-    // polish at 52-57 us instead of 36) and 0.311 with it under the column
-    // solves at a low rate (the KKT pass doubled).  The launch shape
-    // fill_split moves Omega's fill (1) or both (2) after the row-tiled KKT
-    // pass instead.
-    const int early = tu.fill_split == 0 ? 3 : (tu.fill_split == 1 ? 1 : 0);
+    // The zero fill of the outputs goes on the second stream, beside the
+    // covariance kernel (`early`) or the solves after the row-tiled KKT pass
+    const int split = fill_split_for(ctx->tune, L.prec, p * p);
+    const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
     const int late = 3 & ~early;
     if (early) {
         const int v0 = fork_output_fill(ctx, res, p, s, mk, early);
@@ -1504,7 +1512,10 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_pr
     auto *scatter_off = (int64_t *)(h + t.scatter_off);
     col_off[0] = tile_off[0] = kkt_off[0] = split8_off[0] = split4_off[0] = dense_off[0] = scatter_off[0] = 0;
     // the order of fork_output_fill: what the launch shape clears early first
-    const int early = tu.fill_split == 0 ? 3 : (tu.fill_split == 1 ? 1 : 0);
+    int64_t cells = 0;
+    for (int i = 0; i < count; ++i) cells += plans[(size_t)i].p * plans[(size_t)i].p;
+    const int split = fill_split_for(ctx->tune, plans[0].prec, cells);
+    const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
     for (const int which : {early, 3 & ~early}) {
         const std::vector<FillJob> j = batch_fill_jobs(count, res, plans, which);
         std::copy(j.begin(), j.end(), (FillJob *)(h + t.fill) + gr.fills);
@@ -2001,7 +2012,7 @@ int spmesl_autotune(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_op
     cur.dense_block = d.dense_block;
     cur.fill_blocks = d.fill_blocks;
     cur.screen_permille = d.screen_permille;
-    cur.fill_split = d.fill_split;
+    cur.fill_split = fill_split_for(ctx->tune, opt->precision, prob->p * prob->p);
     const size_t tsz = opt->precision == SPMESL_FP64 ? 8 : 4;
     const int rj_max = kkt_rows_per_block(prob->p, tsz, (size_t)160 * 1024);
     cur.kkt_rows = d.kkt_rows > 0 && d.kkt_rows < rj_max ? d.kkt_rows : rj_max;
