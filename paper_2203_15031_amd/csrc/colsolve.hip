@@ -32,15 +32,26 @@
 //            their violators from the pending list, re-solve, and finish with
 //            in-wave KKT passes (rows of S streamed per column).
 // Two tiers: 32-coordinate working sets (four columns per workgroup) and
-// 128-coordinate ones (one per workgroup).  Beyond 128 the column goes to
+// 128-coordinate ones (one per workgroup, whose waves share its KKT passes).  Beyond 128 the column goes to
 // the dense tier (dense.hip), which has no bound on the working set.
 #include "colsolve_dev.hpp"
 
 namespace spmesl {
 
+// A block whose first wave solves columns and whose others help with their
+// KKT passes: the pass to run (go) or the end (not go), and its lists.
+constexpr int kWideWaves = 4;
+template <typename T>
+struct KktTeam {
+    KktCoop coop;
+    int64_t k;
+    int d, w, ns, go;
+    T thr, bthr;
+};
+
 template <typename T, int LW, int KCH, int KU, bool FIRST = false, bool DIRECT = true>
 __device__ void solve_column(const ColArgs<T> &A, WaveSm<T, LW> &sm, int64_t k, int tier, int part = 0,
-                             int nparts = 1, KktCoop *cp = nullptr);
+                             int nparts = 1, KktCoop *cp = nullptr, KktTeam<T> *team = nullptr);
 
 // KCH, KU: groups per lane in flight and support rows per step in the
 // in-wave KKT passes.  NW > 1 (the re-solves of flagged columns): when the
@@ -78,6 +89,54 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(MINW)
         const int64_t k = A.mode ? (int64_t)A.work_list[gw] : A.k0 + gw;
         solve_column<T, LW, KCH, KU, FIRST, DIRECT>(A, sm, k, tier);
     }
+}
+
+// The 128-coordinate tier: the first wave solves the queue's columns, and the
+// block's NW waves share each one's KKT passes, which stream |supp| + 1 rows
+// of S and are bound by the bytes that the waves hold in flight.  next(i)
+// gives the block's i-th column (its problem and index; false at the end),
+// args(d) problem d's arguments.
+template <typename T, int NW, int KCH, int KU, typename F, typename G>
+__device__ __forceinline__ void solve_wide(WaveSm<T, kWMax> &sm, KktTeam<T> &team, F next, G args)
+{
+    static_assert(NW <= kCoopMax, "waves sharing a KKT pass");
+    const int wv = (int)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (wv == 0) {
+        int d;
+        int64_t k;
+        for (int64_t i = 0; next(i, &d, &k); ++i) {
+            if (lane_id() == 0) team.d = d;
+            solve_column<T, kWMax, KCH, KU, false, false>(args(d), sm, k, 1, 0, NW, nullptr, &team);
+        }
+        if (lane_id() == 0) team.go = 0;
+        __syncthreads();
+    } else {
+        for (;;) {
+            __syncthreads();
+            if (!team.go) break;
+            const ColArgs<T> &A = args(team.d);
+            kkt_pass<T, T, kWMax, KCH, KU>(A.S, A.p, A.pv, team.k, sm, team.w, team.ns, team.thr, A.band > T(0),
+                                           team.bthr, A.band_cnt, A.band_idx, wv, NW, &team.coop);
+        }
+    }
+}
+
+template <typename T, int NW, int KCH, int KU>
+__global__ __launch_bounds__(kWave *NW) void k_colsolve_wide(ColArgs<T> A)
+{
+    __shared__ WaveSm<T, kWMax> sm;
+    __shared__ KktTeam<T> team;
+    const int64_t nwork = *A.work_cnt;
+    solve_wide<T, NW, KCH, KU>(
+        sm, team,
+        [&](int64_t i, int *d, int64_t *k) {
+            const int64_t g = (int64_t)blockIdx.x + i * gridDim.x;
+            if (g >= nwork) return false;
+            *d = 0;
+            *k = A.work_list[g];
+            return true;
+        },
+        [&](int) -> const ColArgs<T> & { return A; });
 }
 
 // per-column counters: set by the first solve, accumulated by later phases
@@ -125,7 +184,7 @@ __device__ __forceinline__ void escalate(const ColArgs<T> &A, int64_t k, const W
 
 template <typename T, int LW, int KCH, int KU, bool FIRST, bool DIRECT>
 __device__ __forceinline__ void solve_column(const ColArgs<T> &A, WaveSm<T, LW> &sm, int64_t k, int tier,
-                                             int part, int nparts, KktCoop *cp)
+                                             int part, int nparts, KktCoop *cp, KktTeam<T> *team)
 {
     const int lane = lane_id();
     const bool writer = part == 0;  // the wave that writes the column's results
@@ -275,9 +334,23 @@ __device__ __forceinline__ void solve_column(const ColArgs<T> &A, WaveSm<T, LW> 
 
     while (!FIRST && status == kColOk && !deferred) {
         int ns = build_support(sm, st);
+        KktCoop *lists = cp;
+        if constexpr (LW >= kWMax) {
+            // the block's other waves wait for the pass
+            if (lane == 0) {
+                team->k = k;
+                team->w = st.w;
+                team->ns = ns;
+                team->thr = st.lam_used + A.kkt_tol;
+                team->bthr = st.lam_used - A.band;
+                team->go = 1;
+            }
+            __syncthreads();
+            lists = &team->coop;
+        }
         int npend = kkt_pass<T, T, LW, KCH, KU>(A.S, p, A.pv, k, sm, st.w, ns, st.lam_used + A.kkt_tol, band,
                                                 st.lam_used - A.band, A.band_cnt, A.band_idx, part,
-                                                nparts, cp);
+                                                nparts, lists);
         if (npend == 0) break;
         if (rounds >= A.max_rounds) {
             status = kColNoconv;
@@ -330,16 +403,9 @@ void launch_colsolve(const ColArgs<T> &a, int tier, hipStream_t s)
         hipLaunchKernelGGL((k_colsolve<T, 32, 1, 4, 2, sizeof(T) == 4 ? 3 : 1>), dim3((unsigned)(a.p - a.k0)),
                            dim3(kWave), 0, s, a, 0);
     } else {
-        // the (short) escalation queue, one column per block.  Float: two
-        // waves per block share each column's in-wave KKT passes, which
-        // stream (|supp| + 1) rows of S and dominate these columns at large
-        // p (two 128-coordinate working sets fit the LDS of a block; double
-        // ones do not)
-        unsigned blocks = (unsigned)(a.p < 256 ? a.p : 256);
-        if constexpr (sizeof(T) == 4)
-            hipLaunchKernelGGL((k_colsolve<T, kWMax, 2, 4, 2>), dim3(blocks), dim3(kWave * 2), 0, s, a, 1);
-        else
-            hipLaunchKernelGGL((k_colsolve<T, kWMax, 1, 4, 2>), dim3(blocks), dim3(kWave), 0, s, a, 1);
+        // the (short) escalation queue, one column per block
+        const unsigned blocks = (unsigned)(a.p < 256 ? a.p : 256);
+        hipLaunchKernelGGL((k_colsolve_wide<T, kWideWaves, 4, 2>), dim3(blocks), dim3(kWave * kWideWaves), 0, s, a);
     }
 }
 
@@ -374,6 +440,26 @@ __global__ __launch_bounds__(kWave *NW) void k_colsolve_list_grouped(const ColAr
     }
 }
 
+// The wide tier's queues of many problems.
+template <typename T, int NW, int KCH, int KU>
+__global__ __launch_bounds__(kWave *NW) void k_colsolve_wide_grouped(const ColArgs<T> *__restrict__ tab,
+                                                                     const int64_t *__restrict__ off, int nd)
+{
+    __shared__ WaveSm<T, kWMax> sm;
+    __shared__ KktTeam<T> team;
+    const int64_t total = off[nd];
+    solve_wide<T, NW, KCH, KU>(
+        sm, team,
+        [&](int64_t i, int *d, int64_t *k) {
+            const int64_t g = (int64_t)blockIdx.x + i * gridDim.x;
+            if (g >= total) return false;
+            *d = group_of(off, nd, g);
+            *k = tab[*d].work_list[g - off[*d]];
+            return true;
+        },
+        [&](int d) -> const ColArgs<T> & { return tab[d]; });
+}
+
 template <typename T>
 void launch_colsolve_first_grouped(const ColArgs<T> *tab, const int64_t *off, int nd, int64_t total,
                                    hipStream_t s)
@@ -388,12 +474,9 @@ void launch_colsolve_list_grouped(const ColArgs<T> *tab, const int64_t *off, int
     if (tier == 0) {
         hipLaunchKernelGGL((k_colsolve_list_grouped<T, 32, 4, 4, 4>), dim3(512), dim3(kWave * 4), 0, s, tab, off,
                            nd, 0);
-    } else if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL((k_colsolve_list_grouped<T, kWMax, 2, 4, 2>), dim3(256), dim3(kWave * 2), 0, s, tab,
-                           off, nd, 1);
     } else {
-        hipLaunchKernelGGL((k_colsolve_list_grouped<T, kWMax, 1, 4, 2>), dim3(256), dim3(kWave), 0, s, tab, off,
-                           nd, 1);
+        hipLaunchKernelGGL((k_colsolve_wide_grouped<T, kWideWaves, 4, 2>), dim3(256), dim3(kWave * kWideWaves), 0, s,
+                           tab, off, nd);
     }
 }
 

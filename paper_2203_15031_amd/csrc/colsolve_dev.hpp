@@ -174,17 +174,13 @@ __device__ __forceinline__ int lds_lower_bound(const int *a, int n, int v)
 // when every row of S is 16-byte aligned, i.e. p a multiple of V), CH such
 // groups per trip, and U support rows at a time.
 // ---------------------------------------------------------------------------
+template <typename TS, int V> struct Group {
+    typedef TS type __attribute__((ext_vector_type(V)));
+};
 template <typename TS, int V>
-__device__ __forceinline__ void load_group(const TS *__restrict__ src, TS (&x)[V])
+__device__ __forceinline__ typename Group<TS, V>::type load_group(const TS *__restrict__ src)
 {
-    if constexpr (V == 1) {
-        x[0] = *src;
-    } else {
-        typedef TS vt __attribute__((ext_vector_type(V)));
-        const vt y = *reinterpret_cast<const vt *>(src);
-#pragma unroll
-        for (int e = 0; e < V; ++e) x[e] = y[e];
-    }
+    return *reinterpret_cast<const typename Group<TS, V>::type *>(src);
 }
 
 // Rank of this lane's first element among the flagged elements of a chunk
@@ -237,8 +233,7 @@ __device__ int kkt_pass_v(const TS *__restrict__ S, int64_t p, int64_t jend, int
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int64_t j = base + (int64_t)(c * kWave + lane) * V;
-            TS x[V];
-            load_group<TS, V>(Sk + (j < jend ? j : 0), x);
+            const auto x = load_group<TS, V>(Sk + (j < jend ? j : 0));
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[c][e] = (T)x[e];
         }
@@ -253,13 +248,13 @@ __device__ int kkt_pass_v(const TS *__restrict__ S, int64_t p, int64_t jend, int
                 v[u] = ok ? sm.sval[t + u] : T(0);
                 rows[u] = S + l * p;
             }
-            TS x[U][CH][V];
+            typename Group<TS, V>::type x[U][CH];
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     const int64_t j = base + (int64_t)(c * kWave + lane) * V;
-                    load_group<TS, V>(rows[u] + (j < jend ? j : 0), x[u][c]);
+                    x[u][c] = load_group<TS, V>(rows[u] + (j < jend ? j : 0));
                 }
 #pragma unroll
             for (int u = 0; u < U; ++u)
