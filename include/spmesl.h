@@ -277,7 +277,7 @@ int spmesl_batch_workspace_size(const spmesl_ctx *ctx, int count, const spmesl_p
 typedef struct {
     int32_t dense_block;      /* b, rows per block of the dense tier's delayed
                                  rank-b update (Proposition 2 blocked): 16, 32
-                                 or 64 (default 32) */
+                                 or 64 (default 64) */
     int32_t fill_blocks;      /* workgroups of the dense outputs' zero fill,
                                  which runs beside the covariance kernel
                                  (default 64) */

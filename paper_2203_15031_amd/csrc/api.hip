@@ -53,9 +53,10 @@ constexpr double kMixedFloatTol = 3e-5;
 // instead of 5.3 coordinates per first working set; at 0.7 up to 93% of the
 // columns of a scale-free p = 20000 workload would outgrow 32 coordinates.
 constexpr int kScreenPermille = 800;
-// Rows per block of the dense tier's delayed update, and the largest V whose
+// Rows per block of the dense tier's delayed update (n = 1500, p = 300, double:
+// 6.5 ms a solve with 64, 7.3 with 32, 10.2 with 16), and the largest V whose
 // S[V, V] the double dense tier of the mixed form keeps (8 MB).
-constexpr int kDenseBlock = 32;
+constexpr int kDenseBlock = 64;
 constexpr int64_t kDenseDataMax = 1024;
 // Workgroups of the zero fill of the dense outputs (64 blocks of
 // nontemporal 16-byte stores write about 5 TB/s beside the covariance kernel).

@@ -46,8 +46,9 @@
 // Measured, against 8 waves with gradients and coefficients in global memory
 // and each operand waited for:
 //   n = 1500, p = 300, double (19 groups, V about 300): a group's sweeps and
-//     updates 10.9 -> 6.1 ms, the solve 15.9 -> 11.6 ms, and 8.6 with the LDS tiers'
-//     shorter steps; with 8 waves of 256 registers 5.4 ms, but the full gradient slower;
+//     updates 10.9 -> 6.1 ms, the solve 15.9 -> 11.6 ms, 8.5 with the LDS
+//     tiers' shorter steps, and 6.5 with blocks of 64 rows (of 32: 7.3, of 16:
+//     10.2; half the barriers, each waiting for its slowest column);
 //   n = 400, p = 2500, data form (157 groups, V about 40): 6.0 -> 1.2 ms a
 //     solve: a group's iterations 450 -> 40 us, a full gradient 870 -> 290 us
 //     (its 2 GB of Xt reads a pass come from the caches at 4.4 TB/s).
@@ -667,7 +668,7 @@ __device__ __forceinline__ void run_sweeps(const DenseArgs<T> &A, DenseSm<T> &sm
     const int c = wv;  // this wave's column
     const int tv = (nv + 15) / 16;
     constexpr int NX = kBMax * kBMax / kDT;  // entries of a block's S[J, J] per thread
-    constexpr int PT = 2, PU = 8;            // tiles and steps of the delayed update loaded ahead (b <= 32)
+    constexpr int PT = 2, PU = 8;            // tiles and steps of the delayed update loaded ahead
     const int lb = b <= 16 ? 4 : (b <= 32 ? 5 : 6);
     // this lane's rows of S[V, V] in the wave's first PT tiles (rows past V
     // repeat its last: their results go nowhere).  Here and below no load is
@@ -706,15 +707,13 @@ __device__ __forceinline__ void run_sweeps(const DenseArgs<T> &A, DenseSm<T> &sm
 #pragma unroll
             for (int q = 0; q < NX; ++q)
                 if (q * kDT < b * b) nx[q] = at(vn, (tid + q * kDT) & (b * b - 1));
-            if (b <= 4 * PU) {
 #pragma unroll
-                for (int u = 0; u < PU; ++u) {
-                    const int k = v0 + 4 * u + (lane >> 4);
-                    const int kc = k < nv ? k : nv - 1;
-                    const int64_t col = DATA ? kc : V[kc];
+            for (int u = 0; u < PU; ++u) {
+                const int k = v0 + 4 * u + (lane >> 4);
+                const int kc = k < nv ? k : nv - 1;
+                const int64_t col = DATA ? kc : V[kc];
 #pragma unroll
-                    for (int h = 0; h < PT; ++h) pa[h][u] = prow[h][col];
-                }
+                for (int h = 0; h < PT; ++h) pa[h][u] = prow[h][col];
             }
             // --- the column's sweep of the block ----------------------------
             T dl = T(0);  // this lane's change
@@ -746,7 +745,14 @@ __device__ __forceinline__ void run_sweeps(const DenseArgs<T> &A, DenseSm<T> &sm
                         acc[h][r] = R[rix<LR>(a < (LR ? kVLds : nv) ? a : nv - 1, lane & 15)];
                     }
                 auto change = [&](int64_t k) { return sm.db[lane & 15][k]; };
-                if (b <= 4 * PU && t0 == wv) {
+                const T *row[PT];
+#pragma unroll
+                for (int h = 0; h < PT; ++h) {
+                    const int ra = 16 * (t0 + h * kNW) + (lane & 15);
+                    row[h] = t0 == wv ? prow[h] : vv_row<T, DATA>(A, V, nv, ra < nv ? ra : nv - 1);
+                }
+                int k0 = 0;  // the steps done from the operands loaded ahead
+                if (t0 == wv) {
 #pragma unroll
                     for (int u = 0; u < PU; ++u)
                         if (4 * u < bb) {
@@ -755,16 +761,12 @@ __device__ __forceinline__ void run_sweeps(const DenseArgs<T> &A, DenseSm<T> &sm
                             for (int h = 0; h < PT; ++h)
                                 if (t0 + h * kNW < tv) acc[h] = dmfma(pa[h][u], x, acc[h]);
                         }
-                } else {
-                    const T *row[PT];
-#pragma unroll
-                    for (int h = 0; h < PT; ++h) {
-                        const int ra = 16 * (t0 + h * kNW) + (lane & 15);
-                        row[h] = vv_row<T, DATA>(A, V, nv, ra < nv ? ra : nv - 1);
-                    }
-                    tiles_mma<T, PT, 4>(acc, bb,
-                                        [&](int h, int64_t k) { return vv_at<T, DATA>(row[h], V, v0 + k); }, change);
+                    k0 = bb < 4 * PU ? bb : 4 * PU;
                 }
+                if (k0 < bb)
+                    tiles_mma<T, PT, 4>(
+                        acc, bb - k0, [&](int h, int64_t k) { return vv_at<T, DATA>(row[h], V, v0 + k0 + k); },
+                        [&](int64_t k) { return change(k0 + k); });
 #pragma unroll
                 for (int h = 0; h < PT; ++h)
 #pragma unroll
