@@ -354,7 +354,6 @@ struct spmesl_ctx {
     // outputs, which overlaps the latency-bound column solves
     hipStream_t side = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
-    hipEvent_t fork2 = nullptr, join2 = nullptr;  // statistics reduction beside the scatter
     // per-launch timing (SPMESL_FLAG_TIMING): events in enqueue order, each
     // with the index of the previous event on its stream
     static constexpr int kMaxMarks = 48;
@@ -971,8 +970,8 @@ static StatsJob make_stats_job(const Plan &L, char *ws, Ctl *dctl)
     return j;
 }
 
-// B, sigma and Omega of one problem from its column results (T: double, or
-// float in the float form).
+// B, sigma and Omega, and the statistics, of one problem from its column
+// results (T: double, or float in the float form).
 template <typename T>
 static ScatterJob<T> make_scatter_job(const Plan &L, char *ws, Ctl *dctl, const spmesl_result *res, int original)
 {
@@ -990,6 +989,7 @@ static ScatterJob<T> make_scatter_job(const Plan &L, char *ws, Ctl *dctl, const 
     j.sig_out = res->sigma;
     j.Omega = res->Omega;
     j.flags = &dctl->flags;
+    j.stats = make_stats_job(L, ws, dctl);
     return j;
 }
 
@@ -1085,24 +1085,12 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
         mark(mk, s, "polish");
         enqueue_dense64(q, L, ws, dctl, opt, tu, s, mk);
     }
-    {
-        // the statistics reduction reads only the column results: it runs on
-        // the second stream (behind the fill it may still hold) while the
-        // scatter runs here, and the solve ends when both are done
-        HIPTRY(ctx, hipEventRecord(ctx->fork2, s));
-        HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2, 0));
-        mark(mk, ctx->side, nullptr);
-        launch_reduce_stats(make_stats_job(L, ws, dctl), ctx->side);
-        mark(mk, ctx->side, "reduce_stats");
-        HIPTRY(ctx, hipEventRecord(ctx->join2, ctx->side));
-    }
     if (ev) HIPTRY(ctx, hipEventRecord(ev[4], s));
 
     if (fill) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
     mark(mk, s, "wait_fill");
     enqueue_scatter(L, ws, dctl, res, original, s);
     mark(mk, s, "scatter");
-    HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join2, 0));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[5], s));
     HIPTRY(ctx, hipGetLastError());
     return SPMESL_OK;
@@ -1203,18 +1191,11 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
     launch_dense<double, double>(d, src, s, L.dgroups);
     mark(mk, s, "dense_data_form");
     if (ev) HIPTRY(ctx, hipEventRecord(ev[3], s));
-    HIPTRY(ctx, hipEventRecord(ctx->fork2, s));
-    HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2, 0));
-    mark(mk, ctx->side, nullptr);
-    launch_reduce_stats(make_stats_job(L, ws, dctl), ctx->side);
-    mark(mk, ctx->side, "reduce_stats");
-    HIPTRY(ctx, hipEventRecord(ctx->join2, ctx->side));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[4], s));
     if (res->B || res->Omega) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
     mark(mk, s, "wait_fill");
     enqueue_scatter(L, ws, dctl, res, original, s);
     mark(mk, s, "scatter");
-    HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join2, 0));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[5], s));
     HIPTRY(ctx, hipGetLastError());
     return SPMESL_OK;
@@ -1320,7 +1301,7 @@ static int decode(const Ctl &c, int64_t p, spmesl_stats *st)
 // ---------------------------------------------------------------------------
 struct BatchTabs {
     // uploaded from the host: the tables and the host-known offsets
-    size_t split, first, resume, wide, kkt, polish, syrk, dense, stats, scatter, fill;
+    size_t split, first, resume, wide, kkt, polish, syrk, dense, scatter, fill;
     size_t split8_off, split4_off, col_off, tile_off, kkt_off, dense_off, scatter_off, upload;
     // written on the device: offsets of the device-counted lists
     size_t dirty_off, esc_off, escp_off;
@@ -1339,7 +1320,6 @@ static BatchTabs batch_tabs(int count)
                                    sizeof(DenseJob<double, float>)});
     t.split = b.take(c * sizeof(SplitJob));
     t.dense = b.take(c * dense);
-    t.stats = b.take(c * sizeof(StatsJob));
     t.scatter = b.take(c * std::max(sizeof(ScatterJob<float>), sizeof(ScatterJob<double>)));
     t.fill = b.take(2 * c * sizeof(FillJob));
     t.first = b.take(c * col);
@@ -1563,7 +1543,6 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_pr
         split4_off[i + 1] = split4_off[i] + (sw == 4 ? (L.p + 3) / 4 : 0);
         if (sw == 8) gr.nmax8 = std::max(gr.nmax8, L.n);
         if (sw == 4) gr.nmax4 = std::max(gr.nmax4, L.n);
-        ((StatsJob *)(h + t.stats))[i] = make_stats_job(L, ws, c);
         const int original = opt->output_scale == SPMESL_SCALE_ORIGINAL;
         if (L.prec == SPMESL_FP32)
             ((ScatterJob<float> *)(h + t.scatter))[i] = make_scatter_job<float>(L, ws, c, &res[i], original);
@@ -1643,17 +1622,12 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     } else {
         launch_dense_grouped((const DenseJob<T, T> *)(tb + t.dense), dense_off, count, gr.dense, s);
     }
-    HIPTRY(ctx, hipEventRecord(ctx->fork2, s));
-    HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork2, 0));
-    launch_reduce_stats_grouped((const StatsJob *)(tb + t.stats), count, ctx->side);
-    HIPTRY(ctx, hipEventRecord(ctx->join2, ctx->side));
     if (gr.fills) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
     const auto *scatter_off = (const int64_t *)(tb + t.scatter_off);
     if (plans[0].prec == SPMESL_FP32)
         launch_scatter_grouped((const ScatterJob<float> *)(tb + t.scatter), scatter_off, count, gr.scatter, s);
     else
         launch_scatter_grouped((const ScatterJob<double> *)(tb + t.scatter), scatter_off, count, gr.scatter, s);
-    HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join2, 0));
     HIPTRY(ctx, hipGetLastError());
     return SPMESL_OK;
 }
@@ -1729,8 +1703,6 @@ int spmesl_create(spmesl_ctx **out, int device, void *hip_stream)
     ok = ok && hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ctx->fork2, hipEventDisableTiming) == hipSuccess;
-    ok = ok && hipEventCreateWithFlags(&ctx->join2, hipEventDisableTiming) == hipSuccess;
     bool kok = ok;
     for (int i = 0; i < spmesl_ctx::kMaxMarks && kok; ++i) kok = hipEventCreate(&ctx->kev[i]) == hipSuccess;
     ctx->kev_ok = kok;
@@ -1763,8 +1735,6 @@ void spmesl_destroy(spmesl_ctx *ctx)
             if (ctx->kev[i]) (void)hipEventDestroy(ctx->kev[i]);
         if (ctx->fork) (void)hipEventDestroy(ctx->fork);
         if (ctx->join) (void)hipEventDestroy(ctx->join);
-        if (ctx->fork2) (void)hipEventDestroy(ctx->fork2);
-        if (ctx->join2) (void)hipEventDestroy(ctx->join2);
         if (ctx->ws && ctx->ws_owned) (void)hipFree(ctx->ws);
         if (ctx->tune_status) (void)hipFree(ctx->tune_status);
         if (ctx->pinned) (void)hipHostFree(ctx->pinned);

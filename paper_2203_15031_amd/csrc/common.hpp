@@ -466,7 +466,8 @@ void launch_polish_grouped(const PolishArgs *tab, const int64_t *off, int nd, in
 
 // Reduce the per-column counters and final statuses of one solve into the
 // control block: counters[kNumCounters] and status bits (1 no convergence,
-// 2 degenerate, 4 working set overflow).
+// 2 degenerate, 4 working set overflow), both zeroed at the solve's start.
+// The outputs' scatter does it too.
 struct StatsJob {
     int64_t p;
     const int *colinfo, *polinfo, *w_cnt, *col_status;
@@ -474,7 +475,6 @@ struct StatsJob {
     int *status_bits;
 };
 void launch_reduce_stats(const StatsJob &j, hipStream_t s);
-void launch_reduce_stats_grouped(const StatsJob *tab, int nd, hipStream_t s);
 
 // Zero n 32-bit words (a kernel, so it is safe inside captured graphs).
 void launch_zero_words(uint32_t *a, int64_t n, hipStream_t s);
@@ -496,6 +496,7 @@ struct ScatterJob {
     int original;
     double *B, *sig_out, *Omega;
     const int *flags;
+    StatsJob stats;
 };
 int64_t scatter_blocks(int64_t p);
 template <typename T>

@@ -65,58 +65,57 @@ void launch_zero_words(uint32_t *a, int64_t n, hipStream_t s)
     hipLaunchKernelGGL(k_zero_words, dim3((unsigned)blocks), dim3(256), 0, s, a, n);
 }
 
-// One block: sums and maxima of the per-column counters, status bits from
-// the final per-column statuses.  Each thread takes four columns per pass
-// with every load of the pass in flight together (16-byte loads of the
-// counter records); sums are carried in double (exact below 2^53) through
-// DPP wave reductions, then one LDS step across the block's waves.
-__device__ __forceinline__ void reduce_stats(const StatsJob &J)
+// Sums and maxima of the per-column counters, status bits from the final
+// per-column statuses: block r of reduce_blocks(p), 256 threads, four columns
+// each with every load in flight together (16-byte loads of the counter
+// records).  Sums are carried in double (exact below 2^53) through DPP wave
+// reductions, one LDS step across the block's waves and one atomic per
+// counter and block, into the control block's zeroed words.
+constexpr int kReduceU = 4;
+constexpr int kReduceCols = 256 * kReduceU;
+static int64_t reduce_blocks(int64_t p) { return (p + kReduceCols - 1) / kReduceCols; }
+
+__device__ __forceinline__ void reduce_stats(const StatsJob &J, int64_t r)
 {
-    const int64_t p = J.p;
-    const int *__restrict__ colinfo = J.colinfo, *__restrict__ polinfo = J.polinfo, *__restrict__ w_cnt = J.w_cnt,
-                                *__restrict__ col_status = J.col_status;
-    unsigned long long *__restrict__ counters = J.counters;
     typedef int i4 __attribute__((ext_vector_type(4)));
-    constexpr int U = 4;
+    constexpr int U = kReduceU, NWV = 256 / kWave;
+    const int64_t p = J.p;
     // outer, sweeps, updates, rounds, polish checks, polish added, noconv,
     // final working-set sizes
     double sum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int maxw = 0, maxo = 0, bits = 0;
-    const int64_t nt = blockDim.x;
-    for (int64_t k0 = threadIdx.x; k0 < p; k0 += U * nt) {
-        i4 ci[U], pa[U], pb[U];
-        int wc[U], cs[U];
+    i4 ci[U], pa[U], pb[U];
+    int wc[U], cs[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t k = k0 + u * nt;
-            const bool in = k < p;
-            const i4 z = {0, 0, 0, 0};
-            ci[u] = in ? *reinterpret_cast<const i4 *>(colinfo + k * 4) : z;
-            pa[u] = in && polinfo ? *reinterpret_cast<const i4 *>(polinfo + k * 8) : z;
-            pb[u] = in && polinfo ? *reinterpret_cast<const i4 *>(polinfo + k * 8 + 4) : z;
-            wc[u] = in ? w_cnt[k] : 0;
-            cs[u] = in ? col_status[k] : 0;
-        }
+    for (int u = 0; u < U; ++u) {
+        const int64_t k = r * kReduceCols + u * 256 + threadIdx.x;
+        const bool in = k < p;
+        const i4 z = {0, 0, 0, 0};
+        ci[u] = in ? *reinterpret_cast<const i4 *>(J.colinfo + k * 4) : z;
+        pa[u] = in && J.polinfo ? *reinterpret_cast<const i4 *>(J.polinfo + k * 8) : z;
+        pb[u] = in && J.polinfo ? *reinterpret_cast<const i4 *>(J.polinfo + k * 8 + 4) : z;
+        wc[u] = in ? J.w_cnt[k] : 0;
+        cs[u] = in ? J.col_status[k] : 0;
+    }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            sum[0] += (double)(unsigned)ci[u].x + (double)(unsigned)pa[u].x;
-            sum[1] += (double)(unsigned)ci[u].y + (double)(unsigned)pa[u].y;
-            sum[2] += (double)(unsigned)ci[u].z + (double)(unsigned)pa[u].z;
-            sum[3] += (double)(unsigned)ci[u].w;
-            sum[4] += (double)(unsigned)pa[u].w;
-            sum[5] += (double)(unsigned)pb[u].x;
-            const int o = ci[u].x + pa[u].x;
-            maxo = o > maxo ? o : maxo;
-            maxw = wc[u] > maxw ? wc[u] : maxw;
-            sum[7] += (double)(wc[u] > 0 ? wc[u] : 0);
-            if (cs[u] < 0) {
-                sum[6] += 1.0;
-                bits |= cs[u] == kColWorkset ? 4 : (cs[u] == kColDegenerate ? 2 : 1);
-            }
+    for (int u = 0; u < U; ++u) {
+        sum[0] += (double)(unsigned)ci[u].x + (double)(unsigned)pa[u].x;
+        sum[1] += (double)(unsigned)ci[u].y + (double)(unsigned)pa[u].y;
+        sum[2] += (double)(unsigned)ci[u].z + (double)(unsigned)pa[u].z;
+        sum[3] += (double)(unsigned)ci[u].w;
+        sum[4] += (double)(unsigned)pa[u].w;
+        sum[5] += (double)(unsigned)pb[u].x;
+        const int o = ci[u].x + pa[u].x;
+        maxo = o > maxo ? o : maxo;
+        maxw = wc[u] > maxw ? wc[u] : maxw;
+        sum[7] += (double)(wc[u] > 0 ? wc[u] : 0);
+        if (cs[u] < 0) {
+            sum[6] += 1.0;
+            bits |= cs[u] == kColWorkset ? 4 : (cs[u] == kColDegenerate ? 2 : 1);
         }
     }
-    __shared__ double red[8][32];
-    __shared__ int redi[3][32];
+    __shared__ double red[8][NWV];
+    __shared__ int redi[3][NWV];
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
 #pragma unroll
     for (int i = 0; i < 8; ++i) sum[i] = wave_sum(sum[i]);
@@ -130,46 +129,37 @@ __device__ __forceinline__ void reduce_stats(const StatsJob &J)
         redi[2][wv] = wbits;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = (int)(blockDim.x / kWave);
-        double t[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        int mw = 0, mo = 0, bb = 0;
-        for (int w = 0; w < nw; ++w) {
-            for (int i = 0; i < 8; ++i) t[i] += red[i][w];
-            mw = redi[0][w] > mw ? redi[0][w] : mw;
-            mo = redi[1][w] > mo ? redi[1][w] : mo;
-            bb |= redi[2][w];
+    if (threadIdx.x < 11) {
+        const int i = threadIdx.x;
+        if (i < 8) {
+            const int word = i == 0   ? kCntOuter
+                             : i == 1 ? kCntSweeps
+                             : i == 2 ? kCntUpdates
+                             : i == 3 ? kCntRounds
+                             : i == 4 ? kCntPolishChecks
+                             : i == 5 ? kCntPolishAdded
+                             : i == 6 ? kCntNoconv
+                                      : kCntSumW;
+            double t = 0.0;
+            for (int w = 0; w < NWV; ++w) t += red[i][w];
+            if (t != 0.0) atomicAdd(&J.counters[word], (unsigned long long)t);
+        } else if (i < 10) {
+            int m = 0;
+            for (int w = 0; w < NWV; ++w) m = redi[i - 8][w] > m ? redi[i - 8][w] : m;
+            atomicMax(&J.counters[i == 8 ? kCntMaxW : kCntMaxOuter], (unsigned long long)m);
+        } else {
+            int bb = 0;
+            for (int w = 0; w < NWV; ++w) bb |= redi[2][w];
+            if (bb) atomicOr(J.status_bits, bb);
         }
-        counters[kCntOuter] = (unsigned long long)t[0];
-        counters[kCntSweeps] = (unsigned long long)t[1];
-        counters[kCntUpdates] = (unsigned long long)t[2];
-        counters[kCntRounds] = (unsigned long long)t[3];
-        counters[kCntPolishChecks] = (unsigned long long)t[4];
-        counters[kCntPolishAdded] = (unsigned long long)t[5];
-        counters[kCntNoconv] = (unsigned long long)t[6];
-        counters[kCntSumW] = (unsigned long long)t[7];
-        counters[kCntMaxW] = (unsigned long long)mw;
-        counters[kCntMaxOuter] = (unsigned long long)mo;
-        *J.status_bits = bb;
     }
 }
 
-__global__ __launch_bounds__(1024) void k_reduce_stats(StatsJob J) { reduce_stats(J); }
-
-// (a block per problem)
-__global__ __launch_bounds__(1024) void k_reduce_stats_grouped(const StatsJob *__restrict__ tab)
-{
-    reduce_stats(tab[blockIdx.x]);
-}
+__global__ __launch_bounds__(256) void k_reduce_stats(StatsJob J) { reduce_stats(J, blockIdx.x); }
 
 void launch_reduce_stats(const StatsJob &j, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(1024), 0, s, j);
-}
-
-void launch_reduce_stats_grouped(const StatsJob *tab, int nd, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_reduce_stats_grouped, dim3((unsigned)nd), dim3(1024), 0, s, tab);
+    hipLaunchKernelGGL(k_reduce_stats, dim3((unsigned)reduce_blocks(j.p)), dim3(256), 0, s, j);
 }
 
 __global__ __launch_bounds__(256) void k_fill_zero(double *__restrict__ A, int64_t count)
@@ -237,6 +227,14 @@ template <typename T>
 __device__ __forceinline__ void scatter(const ScatterJob<T> &J, int64_t block)
 {
     const int64_t p = J.p;
+    // the first blocks reduce the statistics, which needs the same results
+    // (on a stream of its own that cost a fork and a join, 10 us a solve)
+    const int64_t rb = (p + kReduceCols - 1) / kReduceCols;
+    if (block < rb) {
+        reduce_stats(J.stats, block);
+        return;
+    }
+    block -= rb;
     const int *__restrict__ w_cnt = J.w_cnt, *__restrict__ w_idx = J.w_idx, *__restrict__ w_off = J.w_off,
                             *__restrict__ flags = J.flags;
     const T *__restrict__ w_beta = J.w_beta;
@@ -306,7 +304,7 @@ __global__ __launch_bounds__(256) void k_scatter_grouped(const ScatterJob<T> *__
     scatter(tab[d], b - off[d]);
 }
 
-int64_t scatter_blocks(int64_t p) { return (p + 3) / 4; }
+int64_t scatter_blocks(int64_t p) { return reduce_blocks(p) + (p + 3) / 4; }
 
 template <typename T>
 void launch_scatter_outputs(const ScatterJob<T> &j, hipStream_t s)
