@@ -287,9 +287,11 @@ typedef struct {
                                  tol}, f in thousandths (default 800) */
     int32_t fill_split;       /* where the zero fill of the dense outputs runs:
                                  0 both beside the covariance kernel, 1 Omega's
-                                 after the row-tiled KKT pass, 2 both after it
-                                 (default, with every field 0: 2 in the float
-                                 and mixed forms from p = 1024, else 0) */
+                                 after the row-tiled KKT pass, 2 both after it.
+                                 With every field 0 the library chooses: in the
+                                 first kernel up to 5 Mi elements per output,
+                                 beyond that 0 in double and 2 in the float and
+                                 mixed forms */
 } spmesl_tuning;
 
 /* Set (NULL: reset to the defaults) or read the context's launch shapes. */

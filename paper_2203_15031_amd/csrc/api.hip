@@ -81,20 +81,26 @@ Tune resolve_tune(const spmesl_tuning &t)
 }
 
 // ... and where the zero fill of `cells` output elements (per output) runs.
-// Shapes that were set decide it; with none set (every field 0) the double
-// form fills beside its covariance kernel, which leaves HBM idle (p = 5000:
-// 0.432 ms a solve against 0.438 with the fills after the KKT pass, p = 1000
-// 0.380 against 0.395), and so does a small problem, whose fill is short
-// (mixed, p = 200: 0.120 against 0.125).  The bf16 and float covariance
-// kernels write S as fast as the fill writes, and the latency-bound solves
-// after the KKT pass are the better company: mixed p = 5000 0.252 against
-// 0.270, p = 20000 4.70 against 5.29, 16 hub networks 0.804 against 0.834,
-// p = 2000 0.400 against 0.407 for two, float p = 2047 0.148 against 0.155.
+// Shapes that were set decide it; with none set (every field 0):
+// * up to 5 Mi elements in the solve's first kernel (kFillFirst): the second
+//   stream's fork and join cost 12-23 us, the two outputs 14 us at p = 2047
+//   (128 us a float solve against 138 with the fills beside the late solves;
+//   mixed p = 2000 174 against 186, p = 500 189 against 210 with the fill
+//   beside the covariance kernel, p = 200 96 against 118, double p = 1000 268
+//   against 282), and 85 us at p = 5000, which is worth hiding;
+// * beyond, in double beside the covariance kernel, which leaves HBM idle
+//   (p = 5000: 0.432 ms a solve against 0.438 with the fills after the KKT
+//   pass).  The bf16 and float kernels write S as fast as the fill writes, and
+//   the latency-bound solves after the KKT pass are the better company: mixed
+//   p = 5000 0.252 against 0.270, p = 20000 4.70 against 5.29, 16 hub networks
+//   0.804 against 0.834.
+constexpr int kFillFirst = 3;
 int fill_split_for(const spmesl_tuning &t, int prec, int64_t cells)
 {
     const bool set = t.dense_block || t.fill_blocks || t.kkt_rows || t.screen_permille || t.fill_split;
     if (set) return t.fill_split;
-    return prec != SPMESL_FP64 && cells >= (int64_t)1 << 20 ? 2 : 0;
+    if (cells < (int64_t)5 << 20) return kFillFirst;
+    return prec != SPMESL_FP64 ? 2 : 0;
 }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1025,14 +1031,19 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
     Marker marker(ctx);
     Marker *mk = ev ? &marker : nullptr;
     mark(mk, s, nullptr);
-    launch_zero_words((uint32_t *)dctl, sizeof(Ctl) / 4, s);
+    // The zero fill of the outputs: in the first kernel, or on the second
+    // stream beside the covariance kernel (`early`) or the solves after the
+    // row-tiled KKT pass
+    const int split = fill_split_for(ctx->tune, L.prec, p * p);
+    const bool first = split == kFillFirst;
+    const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
+    const int late = first ? 0 : 3 & ~early;
+    if (first)
+        launch_zero_start((uint32_t *)dctl, sizeof(Ctl) / 4, FillJob{res->B, p * p}, FillJob{res->Omega, p * p}, s);
+    else
+        launch_zero_words((uint32_t *)dctl, sizeof(Ctl) / 4, s);
     mark(mk, s, "zero_control");
     enqueue_standardize(L, prob, ws, dctl, s, mk);
-    // The zero fill of the outputs goes on the second stream, beside the
-    // covariance kernel (`early`) or the solves after the row-tiled KKT pass
-    const int split = fill_split_for(ctx->tune, L.prec, p * p);
-    const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
-    const int late = 3 & ~early;
     if (early) {
         const int v0 = fork_output_fill(ctx, res, p, s, mk, early);
         if (v0 != SPMESL_OK) return v0;
@@ -1053,7 +1064,7 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
     if (ev) HIPTRY(ctx, hipEventRecord(ev[2], s));
 
 
-    const bool fill = res->B || res->Omega;
+    const bool fill = !first && (res->B || res->Omega);
     auto fork = [&] { return late ? fork_output_fill(ctx, res, p, s, mk, late) : (int)SPMESL_OK; };
     // a warm start: the columns' stored state from B0 and sigma0 (in the
     // scale of the outputs), which the first solves resume from
@@ -1426,7 +1437,8 @@ struct BatchGrids {
     int64_t cols = 0, tiles = 0, kkt_blocks = 0, pmax = 0;
     int64_t split8 = 0, split4 = 0, nmax8 = 0, nmax4 = 0;  // fused standardisations of either width: blocks, most samples
     int64_t dense = 0, scatter = 0;
-    int fill_early = 0, fills = 0;  // fill jobs ahead of the covariance, and all
+    int fill_early = 0, fills = 0;  // fill jobs ahead of the covariance, and all ...
+    bool fill_first = false;        // ... those on the main stream (small totals)
     int rj = 4;
     int syrk_edge = 64;  // covariance tile edge
 };
@@ -1496,7 +1508,8 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_pr
     int64_t cells = 0;
     for (int i = 0; i < count; ++i) cells += plans[(size_t)i].p * plans[(size_t)i].p;
     const int split = fill_split_for(ctx->tune, plans[0].prec, cells);
-    const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
+    gr.fill_first = split == kFillFirst;
+    const int early = gr.fill_first || split == 0 ? 3 : (split == 1 ? 1 : 0);
     for (const int which : {early, 3 & ~early}) {
         const std::vector<FillJob> j = batch_fill_jobs(count, res, plans, which);
         std::copy(j.begin(), j.end(), (FillJob *)(h + t.fill) + gr.fills);
@@ -1593,8 +1606,11 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
         if (!mixed || stats_split_width(plans[(size_t)i].n) == 0)
             enqueue_standardize(plans[(size_t)i], &probs[i], wsi(i), dctl + i, s, nullptr);
     const auto *fill = (const FillJob *)(tb + t.fill);
-    int v = fork_batch_fill(ctx, fill, 0, gr.fill_early, s);
-    if (v != SPMESL_OK) return v;
+    int v = SPMESL_OK;
+    if (gr.fill_first)
+        launch_fill_zero_grouped(fill, gr.fills, s, 1024);
+    else if ((v = fork_batch_fill(ctx, fill, 0, gr.fill_early, s)) != SPMESL_OK)
+        return v;
     if (mixed)
         launch_syrk_bf16x3_grouped((const SyrkJob *)(tb + t.syrk), (const int64_t *)(tb + t.tile_off), count,
                                    gr.tiles, gr.syrk_edge, s);
@@ -1622,7 +1638,7 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     } else {
         launch_dense_grouped((const DenseJob<T, T> *)(tb + t.dense), dense_off, count, gr.dense, s);
     }
-    if (gr.fills) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
+    if (gr.fills && !gr.fill_first) HIPTRY(ctx, hipStreamWaitEvent(s, ctx->join, 0));
     const auto *scatter_off = (const int64_t *)(tb + t.scatter_off);
     if (plans[0].prec == SPMESL_FP32)
         launch_scatter_grouped((const ScatterJob<float> *)(tb + t.scatter), scatter_off, count, gr.scatter, s);
@@ -1984,6 +2000,7 @@ int spmesl_autotune(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_op
     cur.fill_blocks = d.fill_blocks;
     cur.screen_permille = d.screen_permille;
     cur.fill_split = fill_split_for(ctx->tune, opt->precision, prob->p * prob->p);
+    if (cur.fill_split == kFillFirst) cur.fill_split = 0;
     const size_t tsz = opt->precision == SPMESL_FP64 ? 8 : 4;
     const int rj_max = kkt_rows_per_block(prob->p, tsz, (size_t)160 * 1024);
     cur.kkt_rows = d.kkt_rows > 0 && d.kkt_rows < rj_max ? d.kkt_rows : rj_max;

@@ -486,6 +486,8 @@ struct FillJob {
     int64_t count;
 };
 void launch_fill_zero_grouped(const FillJob *tab, int nd, hipStream_t s, int max_blocks);
+// Zero nw words and two arrays (A null: none).
+void launch_zero_start(uint32_t *words, int64_t nw, const FillJob &a, const FillJob &b, hipStream_t s);
 template <typename T>
 struct ScatterJob {
     int64_t p;

@@ -10,6 +10,8 @@
 // a scatter of the few nonzeros.  Proposition 1 maps back to the data's
 // scale: b^o_jk = (c_j / c_k) b_jk, sigma^o_k = sigma_k / c_k,
 // omega^o_jk = c_j c_k omega_jk.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace spmesl {
@@ -196,24 +198,44 @@ void launch_fill_zero(double *A, int64_t count, hipStream_t s, int max_blocks)
     hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)blocks), dim3(256), 0, s, A, count);
 }
 
-// Many arrays in one launch, one after the other by the whole (small) grid.
-__global__ __launch_bounds__(256) void k_fill_zero_grouped(const FillJob *__restrict__ tab, int nd)
+// Thread t0 of `stride` clears its part of an array (that may be only 8-byte
+// aligned: one element, then 16-byte groups).
+__device__ __forceinline__ void fill_array(double *A, int64_t count, int64_t t0, int64_t stride)
 {
     typedef double dv2 __attribute__((ext_vector_type(2)));
     const dv2 z = {0.0, 0.0};
-    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    for (int d = 0; d < nd; ++d) {
-        double *A = tab[d].A;
-        int64_t count = tab[d].count;
-        if (((uintptr_t)A & 15u) != 0) {  // only 8-byte aligned: one element, then 16-byte groups
-            if (t0 == 0) *A = 0.0;
-            ++A;
-            --count;
-        }
-        dv2 *A2 = reinterpret_cast<dv2 *>(A);
-        for (int64_t i = t0; i < count / 2; i += stride) __builtin_nontemporal_store(z, &A2[i]);
-        if (t0 == 0 && (count & 1)) A[count - 1] = 0.0;
+    if (((uintptr_t)A & 15u) != 0) {
+        if (t0 == 0) *A = 0.0;
+        ++A;
+        --count;
     }
+    dv2 *A2 = reinterpret_cast<dv2 *>(A);
+    for (int64_t i = t0; i < count / 2; i += stride) __builtin_nontemporal_store(z, &A2[i]);
+    if (t0 == 0 && (count & 1)) A[count - 1] = 0.0;
+}
+
+// Many arrays in one launch, one after the other by the whole (small) grid.
+__global__ __launch_bounds__(256) void k_fill_zero_grouped(const FillJob *__restrict__ tab, int nd)
+{
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int d = 0; d < nd; ++d) fill_array(tab[d].A, tab[d].count, t0, stride);
+}
+
+// Zero nw words and the two arrays (either may be null) in one launch.
+__global__ __launch_bounds__(256) void k_zero_start(uint32_t *__restrict__ words, int64_t nw, FillJob a, FillJob b)
+{
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = t0; i < nw; i += stride) words[i] = 0u;
+    if (a.A) fill_array(a.A, a.count, t0, stride);
+    if (b.A) fill_array(b.A, b.count, t0, stride);
+}
+
+void launch_zero_start(uint32_t *words, int64_t nw, const FillJob &a, const FillJob &b, hipStream_t s)
+{
+    // four 16-byte groups of an array a thread
+    const int64_t count = std::max(std::max(a.A ? a.count : 0, b.A ? b.count : 0) / 8, nw);
+    const int64_t blocks = std::min<int64_t>((count + 255) / 256 + 1, 1024);
+    hipLaunchKernelGGL(k_zero_start, dim3((unsigned)blocks), dim3(256), 0, s, words, nw, a, b);
 }
 
 void launch_fill_zero_grouped(const FillJob *tab, int nd, hipStream_t s, int max_blocks)

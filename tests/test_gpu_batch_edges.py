@@ -50,3 +50,21 @@ def test_batch_edges(ctx, prec):
             b = o["buf"]  # nothing written beside the outputs
             keep = [0, 1 + p * p, 2 + 2 * p * p]
             assert bool((b[keep] == 7.0).all())
+
+
+@pytest.mark.parametrize("p", [2, 33, 600])
+def test_outputs_of_a_small_solve(ctx, p):
+    # cleared by the solve's first kernel: 8-byte aligned, nothing beside them
+    rng = np.random.default_rng(p)
+    X = torch.from_numpy(rng.standard_normal((80, p)) + 0.5 * rng.standard_normal((80, 1))).to("cuda:0")
+    ref = ctx.solve(X, 0.3, tol=1e-8, precision="mixed")
+    for skip in (None, "B", "Omega"):
+        buf = torch.full((2 * p * p + 3,), 7.0, dtype=torch.float64, device="cuda:0")
+        out = dict(B=buf[1:1 + p * p].view(p, p), Omega=buf[2 + p * p:2 + 2 * p * p].view(p, p))
+        want = [k for k in ("B", "Omega") if k != skip]
+        for k in want:
+            buf.fill_(7.0)
+            ctx.solve(X, 0.3, tol=1e-8, precision="mixed", out={q: out[q] for q in want}, want=tuple(want))
+        for k in want:
+            assert torch.equal(out[k], getattr(ref, k))
+        assert bool((buf[[0, 1 + p * p, 2 + 2 * p * p]] == 7.0).all())
