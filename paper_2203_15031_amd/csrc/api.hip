@@ -80,6 +80,11 @@ Tune resolve_tune(const spmesl_tuning &t)
     return u;
 }
 
+bool tuning_set(const spmesl_tuning &t)
+{
+    return t.dense_block || t.fill_blocks || t.kkt_rows || t.screen_permille || t.fill_split;
+}
+
 // ... and where the zero fill of `cells` output elements (per output) runs.
 // Shapes that were set decide it; with none set (every field 0):
 // * up to 5 Mi elements in the solve's first kernel (kFillFirst): the second
@@ -92,13 +97,13 @@ Tune resolve_tune(const spmesl_tuning &t)
 //   (p = 5000: 0.432 ms a solve against 0.438 with the fills after the KKT
 //   pass).  The bf16 and float kernels write S as fast as the fill writes, and
 //   the latency-bound solves after the KKT pass are the better company: mixed
-//   p = 5000 0.252 against 0.270, p = 20000 4.70 against 5.29, 16 hub networks
-//   0.804 against 0.834.
+//   p = 5000 0.240 against 0.250, p = 3000 0.171 against 0.182, p = 20000 4.70
+//   against 5.29; float p = 5000 0.326 against 0.336; 16 hub networks 0.804
+//   against 0.834.
 constexpr int kFillFirst = 3;
 int fill_split_for(const spmesl_tuning &t, int prec, int64_t cells)
 {
-    const bool set = t.dense_block || t.fill_blocks || t.kkt_rows || t.screen_permille || t.fill_split;
-    if (set) return t.fill_split;
+    if (tuning_set(t)) return t.fill_split;
     if (cells < (int64_t)5 << 20) return kFillFirst;
     return prec != SPMESL_FP64 ? 2 : 0;
 }
@@ -1421,12 +1426,12 @@ static std::vector<FillJob> batch_fill_jobs(int count, const spmesl_result *res,
 }
 
 // Clear fill jobs [j0, j1) of the batch's table on the second stream.
-static int fork_batch_fill(spmesl_ctx *ctx, const FillJob *tab, int j0, int j1, hipStream_t s)
+static int fork_batch_fill(spmesl_ctx *ctx, const FillJob *tab, int j0, int j1, int blocks, hipStream_t s)
 {
     if (j0 >= j1) return SPMESL_OK;
     HIPTRY(ctx, hipEventRecord(ctx->fork, s));
     HIPTRY(ctx, hipStreamWaitEvent(ctx->side, ctx->fork, 0));
-    launch_fill_zero_grouped(tab + j0, j1 - j0, ctx->side, resolve_tune(ctx->tune).fill_blocks);
+    launch_fill_zero_grouped(tab + j0, j1 - j0, ctx->side, blocks);
     HIPTRY(ctx, hipEventRecord(ctx->join, ctx->side));
     return SPMESL_OK;
 }
@@ -1439,6 +1444,7 @@ struct BatchGrids {
     int64_t dense = 0, scatter = 0;
     int fill_early = 0, fills = 0;  // fill jobs ahead of the covariance, and all ...
     bool fill_first = false;        // ... those on the main stream (small totals)
+    int fill_blocks = kFillBlocks;
     int rj = 4;
     int syrk_edge = 64;  // covariance tile edge
 };
@@ -1507,7 +1513,13 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_pr
     // the order of fork_output_fill: what the launch shape clears early first
     int64_t cells = 0;
     for (int i = 0; i < count; ++i) cells += plans[(size_t)i].p * plans[(size_t)i].p;
-    const int split = fill_split_for(ctx->tune, plans[0].prec, cells);
+    // A batch's late solves are short beside the fills of a large total: beyond
+    // 32 Mi elements they run beside the covariance tiles (eight mixed data
+    // sets of p = 5000: 1.94 ms against 2.07 after the KKT pass, with 256
+    // blocks 1.86; float 2.05 against 2.42, and 2.25 with 256).
+    const bool large = cells > (int64_t)32 << 20 && !tuning_set(ctx->tune);
+    const int split = large ? 0 : fill_split_for(ctx->tune, plans[0].prec, cells);
+    gr.fill_blocks = large && plans[0].prec == SPMESL_MIXED ? 256 : tu.fill_blocks;
     gr.fill_first = split == kFillFirst;
     const int early = gr.fill_first || split == 0 ? 3 : (split == 1 ? 1 : 0);
     for (const int which : {early, 3 & ~early}) {
@@ -1609,7 +1621,7 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     int v = SPMESL_OK;
     if (gr.fill_first)
         launch_fill_zero_grouped(fill, gr.fills, s, 1024);
-    else if ((v = fork_batch_fill(ctx, fill, 0, gr.fill_early, s)) != SPMESL_OK)
+    else if ((v = fork_batch_fill(ctx, fill, 0, gr.fill_early, gr.fill_blocks, s)) != SPMESL_OK)
         return v;
     if (mixed)
         launch_syrk_bf16x3_grouped((const SyrkJob *)(tb + t.syrk), (const int64_t *)(tb + t.tile_off), count,
@@ -1620,7 +1632,7 @@ static int enqueue_batch_grouped(spmesl_ctx *ctx, int count, const spmesl_proble
     launch_colsolve_first_grouped<T>((const ColArgs<T> *)(tb + t.first), col_off, count, gr.cols, s);
     launch_kkt_rows_grouped<T>((const KktJob<T> *)(tb + t.kkt), (const int64_t *)(tb + t.kkt_off), count,
                                gr.kkt_blocks, gr.rj, gr.pmax, s);
-    if ((v = fork_batch_fill(ctx, fill, gr.fill_early, gr.fills, s)) != SPMESL_OK) return v;
+    if ((v = fork_batch_fill(ctx, fill, gr.fill_early, gr.fills, gr.fill_blocks, s)) != SPMESL_OK) return v;
     // re-solves of the flagged columns, then every escalated column (the
     // first solves' and the re-solves') in the wide tier
     launch_group_offsets(&dctl->dirty, ctl_words, count, dirty_off, s);
