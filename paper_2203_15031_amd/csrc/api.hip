@@ -561,6 +561,14 @@ static int validate(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_op
     return SPMESL_OK;
 }
 
+// Whether `cells` doubles at `out` share memory with the rows of a matrix
+// (rows x cols, stride ld): such an output is not cleared before the matrix
+// has been read.
+static bool shares_memory(const double *out, int64_t cells, const double *x, int64_t rows, int64_t cols, int64_t ld)
+{
+    return out && x && out < x + (rows - 1) * ld + cols && x < out + cells;
+}
+
 // The zero fill of the dense outputs needs nothing of the solve: it is
 // forked onto the context's second stream at a point where the main stream
 // leaves HBM to it (chosen per form by the caller), and the scatter waits
@@ -1039,7 +1047,10 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
     // The zero fill of the outputs: in the first kernel, or on the second
     // stream beside the covariance kernel (`early`) or the solves after the
     // row-tiled KKT pass
-    const int split = fill_split_for(ctx->tune, L.prec, p * p);
+    int split = fill_split_for(ctx->tune, L.prec, p * p);
+    if (split == kFillFirst && (shares_memory(res->B, p * p, prob->X, n, p, prob->ldx) ||
+                                shares_memory(res->Omega, p * p, prob->X, n, p, prob->ldx)))
+        split = 0;
     const bool first = split == kFillFirst;
     const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
     const int late = first ? 0 : 3 & ~early;

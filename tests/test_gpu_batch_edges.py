@@ -68,3 +68,14 @@ def test_outputs_of_a_small_solve(ctx, p):
         for k in want:
             assert torch.equal(out[k], getattr(ref, k))
         assert bool((buf[[0, 1 + p * p, 2 + 2 * p * p]] == 7.0).all())
+
+
+def test_output_in_the_inputs_memory(ctx):
+    # an output that overlaps X is cleared only once X has been read
+    rng = np.random.default_rng(5)
+    n = p = 70
+    X = torch.from_numpy(rng.standard_normal((n, p))).to("cuda:0")
+    ref = ctx.solve(X, 0.4, tol=1e-8, precision="mixed")
+    Xc = X.clone()
+    r = ctx.solve(Xc, 0.4, tol=1e-8, precision="mixed", out=dict(B=Xc, sigma=ref.sigma.clone()), want=("B", "sigma"))
+    assert torch.equal(r.B, ref.B) and torch.equal(r.sigma, ref.sigma)
