@@ -242,17 +242,18 @@ __device__ __forceinline__ int compact_v(const DenseArgs<T> &A, DenseSm<T> &sm)
     return base;
 }
 
-// V from the marks; when it covers 15/16 of all rows (and at most `cap` rows
-// fit) the others are taken as well.  A row that a full gradient adds later
+// V from the marks; when it covers 15/16 of the predictors (j < pv: a scaled
+// lasso's responses follow them and never enter V) and all of them fit `cap`
+// rows, the others are taken as well.  A row that a full gradient adds later
 // costs the group a new S on V and all its sweeps again, where a row too many
-// costs at most 1/8 more per sweep; and with every row in V, no result depends
-// on which columns the queue's order puts into a group.
+// costs at most 1/8 more per sweep; and with every predictor in V, no result
+// depends on which columns the queue's order puts into a group.
 template <typename T>
 __device__ __forceinline__ int build_v(const DenseArgs<T> &A, DenseSm<T> &sm, int64_t cap)
 {
     const int nv = compact_v(A, sm);
-    if (nv >= A.p || A.p > cap || 16 * (int64_t)nv < 15 * A.p) return nv;
-    for (int64_t j = threadIdx.x; j < A.p; j += kDT) A.mark[j] = 1;
+    if (nv >= A.pv || A.pv > cap || 16 * (int64_t)nv < 15 * A.pv) return nv;
+    for (int64_t j = threadIdx.x; j < A.pv; j += kDT) A.mark[j] = 1;
     __syncthreads();
     return compact_v(A, sm);
 }
