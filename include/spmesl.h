@@ -111,7 +111,8 @@ typedef struct {
      * number starts that column at sigma = 1).  The minimiser is unique, so
      * a warm start changes the work, not the result: it resumes a solve that
      * stopped at an iteration cap (SPMESL_ENOCONV), or follows a path of
-     * penalties.  Ignored by spmesl_covariance; spmesl_scaled_lasso refuses
+     * penalties.  B0 and sigma0 may be the outputs of the same call: they are
+     * read before the outputs are written.  Ignored by spmesl_covariance; spmesl_scaled_lasso refuses
      * it (SPMESL_EINVAL). */
     const double *B0;
     const double *sigma0;

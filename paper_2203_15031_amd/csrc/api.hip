@@ -561,12 +561,23 @@ static int validate(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_op
     return SPMESL_OK;
 }
 
-// Whether `cells` doubles at `out` share memory with the rows of a matrix
-// (rows x cols, stride ld): such an output is not cleared before the matrix
-// has been read.
-static bool shares_memory(const double *out, int64_t cells, const double *x, int64_t rows, int64_t cols, int64_t ld)
+// Whether an output that is cleared (B or Omega) shares memory with the rows
+// of an input matrix (rows x cols, stride ld): it is not cleared before the
+// input has been read, X by the standardisation, a warm start (a result passed
+// back in, say) by k_warm_start.
+static bool shares_memory(const spmesl_result *res, int64_t p, const double *x, int64_t rows, int64_t cols, int64_t ld)
 {
-    return out && x && out < x + (rows - 1) * ld + cols && x < out + cells;
+    auto on = [&](const double *out) { return out && out < x + (rows - 1) * ld + cols && x < out + p * p; };
+    return x && (on(res->B) || on(res->Omega));
+}
+static bool on_input(const spmesl_result *res, const spmesl_problem *prob)
+{
+    return shares_memory(res, prob->p, prob->X, prob->n, prob->p, prob->ldx);
+}
+static bool on_warm_start(const spmesl_result *res, const spmesl_problem *prob)
+{
+    return shares_memory(res, prob->p, prob->B0, prob->p, prob->p, prob->p) ||
+           shares_memory(res, prob->p, prob->sigma0, 1, prob->p, prob->p);
 }
 
 // The zero fill of the dense outputs needs nothing of the solve: it is
@@ -1046,11 +1057,10 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
     mark(mk, s, nullptr);
     // The zero fill of the outputs: in the first kernel, or on the second
     // stream beside the covariance kernel (`early`) or the solves after the
-    // row-tiled KKT pass
+    // row-tiled KKT pass (the only place that follows the warm start)
     int split = fill_split_for(ctx->tune, L.prec, p * p);
-    if (split == kFillFirst && (shares_memory(res->B, p * p, prob->X, n, p, prob->ldx) ||
-                                shares_memory(res->Omega, p * p, prob->X, n, p, prob->ldx)))
-        split = 0;
+    if (on_warm_start(res, prob)) split = 2;
+    else if (split == kFillFirst && on_input(res, prob)) split = 0;
     const bool first = split == kFillFirst;
     const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
     const int late = first ? 0 : 3 & ~early;
@@ -1153,7 +1163,8 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
         launch_standardize_split(prob->X, n, p, prob->ldx, mean, scale, (double *)(ws + L.xt), nullptr, L.npad, s);
     }
     mark(mk, s, "standardize");
-    const int v0 = fork_output_fill(ctx, res, p, s, mk);
+    const bool after_warm = on_warm_start(res, prob);
+    int v0 = after_warm ? (int)SPMESL_OK : fork_output_fill(ctx, res, p, s, mk);
     if (v0 != SPMESL_OK) return v0;
     if (ev) HIPTRY(ctx, hipEventRecord(ev[1], s));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[2], s));
@@ -1164,6 +1175,7 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
                                   (double *)(ws + L.lam), (int *)(ws + L.cstat), s);
         mark(mk, s, "warm_start");
     }
+    if (after_warm && (v0 = fork_output_fill(ctx, res, p, s, mk)) != SPMESL_OK) return v0;
     DenseArgs<double> d{};
     d.S = nullptr;
     d.Xt = (const double *)(ws + L.xt);
