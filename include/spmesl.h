@@ -279,20 +279,24 @@ typedef struct {
     int32_t dense_block;      /* b, rows per block of the dense tier's delayed
                                  rank-b update (Proposition 2 blocked): 16, 32
                                  or 64 (default 64) */
-    int32_t fill_blocks;      /* workgroups of the dense outputs' zero fill,
-                                 which runs beside the covariance kernel
-                                 (default 64) */
+    int32_t fill_blocks;      /* workgroups of the dense outputs' zero fill
+                                 where it runs on the second stream (default
+                                 64; a mixed batch of more than 32 Mi elements
+                                 takes four times as many) */
     int32_t kkt_rows;         /* rows of S per tile of the row-tiled KKT pass:
                                  1, 2 or 4 (default: the most that fit LDS) */
     int32_t screen_permille;  /* first working sets {j : |s_jk| > f lambda0 +
                                  tol}, f in thousandths (default 800) */
     int32_t fill_split;       /* where the zero fill of the dense outputs runs:
-                                 0 both beside the covariance kernel, 1 Omega's
-                                 after the row-tiled KKT pass, 2 both after it.
-                                 With every field 0 the library chooses: in the
-                                 first kernel up to 5 Mi elements per output,
-                                 beyond that 0 in double and 2 in the float and
-                                 mixed forms */
+                                 0 the library chooses, whatever the other
+                                 fields hold (up to 5 Mi elements per output
+                                 the first kernel; beyond that beside the
+                                 covariance kernel in double and after the
+                                 row-tiled KKT pass in the float and mixed
+                                 forms; a batch of more than 32 Mi elements
+                                 beside the covariance tiles), 1 B's beside
+                                 the covariance kernel and Omega's after the
+                                 row-tiled KKT pass, 2 both after it */
 } spmesl_tuning;
 
 /* Set (NULL: reset to the defaults) or read the context's launch shapes. */
@@ -305,8 +309,10 @@ int spmesl_get_tuning(const spmesl_ctx *ctx, spmesl_tuning *t);
  * of each field in turn (coordinate search from the current shapes: screen
  * 700/800/900/1000, KKT rows 4/2/1 as they fit, fill 32/64/128/256
  * workgroups, fill placement 0/1/2, dense block 16/32/64 when the problem
- * reaches the dense tier),
- * keeps the fastest, sets it on the context and writes it to *best (host,
+ * reaches the dense tier).  The shapes found are then timed against the
+ * defaults as repeated calls run them (graph replays; at most two of the
+ * context's graphs), and the defaults are kept unless they are at least 1%
+ * slower.  Sets the result on the context and writes it to *best (host,
  * may be NULL) with its time per solve in *ms_best (host, may be NULL).  The
  * outputs in `res` hold the last solve's result.  Allocates (workspace,
  * graphs, a status word).  Returns SPMESL_OK or the first error of a solve. */

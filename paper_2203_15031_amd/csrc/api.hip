@@ -80,13 +80,8 @@ Tune resolve_tune(const spmesl_tuning &t)
     return u;
 }
 
-bool tuning_set(const spmesl_tuning &t)
-{
-    return t.dense_block || t.fill_blocks || t.kkt_rows || t.screen_permille || t.fill_split;
-}
-
-// ... and where the zero fill of `cells` output elements (per output) runs.
-// Shapes that were set decide it; with none set (every field 0):
+// ... and where the zero fill of `cells` output elements (per output) runs:
+// the placement that was set, or (0, whatever the other fields hold)
 // * up to 5 Mi elements in the solve's first kernel (kFillFirst): the second
 //   stream's fork and join cost 12-23 us, the two outputs 14 us at p = 2047
 //   (128 us a float solve against 138 with the fills beside the late solves;
@@ -100,12 +95,12 @@ bool tuning_set(const spmesl_tuning &t)
 //   p = 5000 0.240 against 0.250, p = 3000 0.171 against 0.182, p = 20000 4.70
 //   against 5.29; float p = 5000 0.326 against 0.336; 16 hub networks 0.804
 //   against 0.834.
-constexpr int kFillFirst = 3;
+constexpr int kFillFirst = 3, kFillEarly = 0;
 int fill_split_for(const spmesl_tuning &t, int prec, int64_t cells)
 {
-    if (tuning_set(t)) return t.fill_split;
+    if (t.fill_split) return t.fill_split;
     if (cells < (int64_t)5 << 20) return kFillFirst;
-    return prec != SPMESL_FP64 ? 2 : 0;
+    return prec != SPMESL_FP64 ? 2 : kFillEarly;
 }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -1060,9 +1055,9 @@ static int enqueue_solve(spmesl_ctx *ctx, const spmesl_problem *prob, const spme
     // row-tiled KKT pass (the only place that follows the warm start)
     int split = fill_split_for(ctx->tune, L.prec, p * p);
     if (on_warm_start(res, prob)) split = 2;
-    else if (split == kFillFirst && on_input(res, prob)) split = 0;
+    else if (split == kFillFirst && on_input(res, prob)) split = kFillEarly;
     const bool first = split == kFillFirst;
-    const int early = split == 0 ? 3 : (split == 1 ? 1 : 0);
+    const int early = split == kFillEarly ? 3 : (split == 1 ? 1 : 0);
     const int late = first ? 0 : 3 & ~early;
     if (first)
         launch_zero_start((uint32_t *)dctl, sizeof(Ctl) / 4, FillJob{res->B, p * p}, FillJob{res->Omega, p * p}, s);
@@ -1538,13 +1533,13 @@ static BatchGrids build_batch_tables(spmesl_ctx *ctx, int count, const spmesl_pr
     for (int i = 0; i < count; ++i) cells += plans[(size_t)i].p * plans[(size_t)i].p;
     // A batch's late solves are short beside the fills of a large total: beyond
     // 32 Mi elements they run beside the covariance tiles (eight mixed data
-    // sets of p = 5000: 1.94 ms against 2.07 after the KKT pass, with 256
-    // blocks 1.86; float 2.05 against 2.42, and 2.25 with 256).
-    const bool large = cells > (int64_t)32 << 20 && !tuning_set(ctx->tune);
-    const int split = large ? 0 : fill_split_for(ctx->tune, plans[0].prec, cells);
-    gr.fill_blocks = large && plans[0].prec == SPMESL_MIXED ? 256 : tu.fill_blocks;
+    // sets of p = 5000: 1.94 ms against 2.07 after the KKT pass, with four
+    // times the blocks 1.86; float 2.05 against 2.42, and 2.25 with 256).
+    const bool large = cells > (int64_t)32 << 20 && ctx->tune.fill_split == 0;
+    const int split = large ? kFillEarly : fill_split_for(ctx->tune, plans[0].prec, cells);
+    gr.fill_blocks = large && plans[0].prec == SPMESL_MIXED ? 4 * tu.fill_blocks : tu.fill_blocks;
     gr.fill_first = split == kFillFirst;
-    const int early = gr.fill_first || split == 0 ? 3 : (split == 1 ? 1 : 0);
+    const int early = gr.fill_first || split == kFillEarly ? 3 : (split == 1 ? 1 : 0);
     for (const int which : {early, 3 & ~early}) {
         const std::vector<FillJob> j = batch_fill_jobs(count, res, plans, which);
         std::copy(j.begin(), j.end(), (FillJob *)(h + t.fill) + gr.fills);
@@ -1989,20 +1984,24 @@ int spmesl_get_tuning(const spmesl_ctx *ctx, spmesl_tuning *t)
 }
 
 // Milliseconds per solve: the fastest of three runs of `reps` asynchronous
-// solves back to back, kernel by kernel.  The minimum over runs keeps other
-// work on the device out of the comparison.
+// solves back to back, kernel by kernel or (`replay`) as a repeated call runs
+// them.  The minimum over runs keeps other work on the device out of the
+// comparison.
 static int time_solves(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_options *opt,
-                       spmesl_result *res, int reps, double *ms)
+                       spmesl_result *res, int reps, bool replay, double *ms)
 {
     spmesl_options o = *opt;
-    o.flags = (o.flags & ~SPMESL_FLAG_TIMING) | SPMESL_FLAG_EAGER;  // one graph per candidate would stay for good
+    o.flags = (o.flags & ~SPMESL_FLAG_TIMING) | SPMESL_FLAG_EAGER;
     int v = spmesl_solve(ctx, prob, &o, res);  // checks the status
     if (v != SPMESL_OK) return v;
+    if (replay) o.flags = opt->flags & ~SPMESL_FLAG_TIMING;
     DevGuard g(ctx->device);
     double best = 0.0;
-    for (int run = 0; run < 3; ++run) {
+    // (a repeated call: kernel by kernel, captured, and then replayed)
+    for (int run = replay ? -2 : 0; run < 3; ++run) {
+        const int m = run < 0 ? 1 : reps;
         HIPTRY(ctx, hipEventRecord(ctx->ev[0], ctx->stream));
-        for (int r = 0; r < reps; ++r) {
+        for (int r = 0; r < m; ++r) {
             v = spmesl_solve_async(ctx, prob, &o, res, ctx->tune_status);
             if (v != SPMESL_OK) return v;
         }
@@ -2010,8 +2009,8 @@ static int time_solves(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl
         HIPTRY(ctx, hipEventSynchronize(ctx->ev[1]));
         float t = 0.f;
         HIPTRY(ctx, hipEventElapsedTime(&t, ctx->ev[0], ctx->ev[1]));
-        const double m = (double)t / reps;
-        best = run == 0 || m < best ? m : best;
+        const double per = (double)t / m;
+        best = run <= 0 || per < best ? per : best;
     }
     *ms = best;
     return SPMESL_OK;
@@ -2028,20 +2027,27 @@ int spmesl_autotune(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_op
         DevGuard g(ctx->device);
         if (!ctx->tune_status) HIPTRY(ctx, hipMalloc((void **)&ctx->tune_status, sizeof(int)));
     }
-    // explicit values for every field, starting from the current shapes
-    const Tune d = resolve_tune(ctx->tune);
-    spmesl_tuning cur{};
-    cur.dense_block = d.dense_block;
-    cur.fill_blocks = d.fill_blocks;
-    cur.screen_permille = d.screen_permille;
-    cur.fill_split = fill_split_for(ctx->tune, opt->precision, prob->p * prob->p);
-    if (cur.fill_split == kFillFirst) cur.fill_split = 0;
+    // explicit values for every field but the fills' placement (0: the
+    // library's choice), starting from the current shapes
     const size_t tsz = opt->precision == SPMESL_FP64 ? 8 : 4;
     const int rj_max = kkt_rows_per_block(prob->p, tsz, (size_t)160 * 1024);
-    cur.kkt_rows = d.kkt_rows > 0 && d.kkt_rows < rj_max ? d.kkt_rows : rj_max;
+    auto shapes = [&](const spmesl_tuning &t) {
+        const Tune d = resolve_tune(t);
+        spmesl_tuning u{};
+        u.dense_block = d.dense_block;
+        u.fill_blocks = d.fill_blocks;
+        u.screen_permille = d.screen_permille;
+        u.fill_split = t.fill_split;
+        u.kkt_rows = d.kkt_rows > 0 && d.kkt_rows < rj_max ? d.kkt_rows : rj_max;
+        return u;
+    };
+    const spmesl_tuning def = shapes(spmesl_tuning{});
+    spmesl_tuning cur = shapes(ctx->tune);
     ctx->tune = cur;
+    // the candidates are timed kernel by kernel: a graph of each would stay
+    // for good (see run_graph)
     double tbest = 0.0;
-    v = time_solves(ctx, prob, opt, res, reps, &tbest);
+    v = time_solves(ctx, prob, opt, res, reps, false, &tbest);
     if (v != SPMESL_OK) return v;
     // does the problem reach the dense tier?  (its block size matters only then)
     spmesl_stats st{};
@@ -2057,7 +2063,7 @@ int spmesl_autotune(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_op
             t.*field = c;
             ctx->tune = t;
             double ms = 0.0;
-            const int r = time_solves(ctx, prob, opt, res, reps, &ms);
+            const int r = time_solves(ctx, prob, opt, res, reps, false, &ms);
             if (r != SPMESL_OK) return r;
             // a candidate replaces the current shapes only when clearly faster
             if (ms < 0.99 * tbest) {
@@ -2077,6 +2083,17 @@ int spmesl_autotune(spmesl_ctx *ctx, const spmesl_problem *prob, const spmesl_op
     if ((v = search(&spmesl_tuning::fill_blocks, {32, 64, 128, 256})) != SPMESL_OK) return v;
     if ((v = search(&spmesl_tuning::fill_split, {0, 1, 2})) != SPMESL_OK) return v;
     if (dense && (v = search(&spmesl_tuning::dense_block, {16, 32, 64})) != SPMESL_OK) return v;
+    // what was found replaces the defaults only where repeated calls, which
+    // replay graphs, are clearly faster with it
+    ctx->tune = def;
+    if ((v = time_solves(ctx, prob, opt, res, reps, true, &tbest)) != SPMESL_OK) return v;
+    if (std::memcmp(&cur, &def, sizeof cur) != 0) {
+        double ms = 0.0;
+        ctx->tune = cur;
+        if ((v = time_solves(ctx, prob, opt, res, reps, true, &ms)) != SPMESL_OK) return v;
+        if (ms < 0.99 * tbest) tbest = ms;
+        else cur = def;
+    }
     ctx->tune = cur;
     // the outputs hold a solve with the chosen shapes
     v = spmesl_solve(ctx, prob, opt, res);
