@@ -134,9 +134,12 @@ typedef struct {
 
 #define SPMESL_FLAG_TIMING 1
 /* Enqueue the kernels one by one instead of replaying the context's cached
- * HIP graph of the call (the default for calls that repeat the pointers,
- * sizes and options of one of the last calls; timed calls are always
- * eager). */
+ * HIP graph of the call.  By default a call that repeats the pointers, sizes
+ * and options of one of the context's last four distinct calls is captured,
+ * and its further repeats are one graph launch (timed calls are always
+ * eager).  A context keeps its graphs until it is destroyed, also those of a
+ * workspace it no longer uses, and at most 64 of them: past that, calls it
+ * holds no graph of run kernel by kernel, and a new context starts afresh. */
 #define SPMESL_FLAG_EAGER 2
 /* Mixed form: the double polish proves every column by a full pass over S
  * (every j with |g_j| within the float error bound of lambda joins the

@@ -378,6 +378,10 @@ struct spmesl_ctx {
     };
     static constexpr size_t kMaxGraphs = 64;
     std::vector<CachedGraph> graphs;
+    // the stream the last of them was launched on, and whether others were
+    // launched on another
+    hipStream_t graph_stream = nullptr;
+    bool graph_launched = false, graph_left = false;
     // the last distinct calls that ran kernel by kernel, most recent first
     static constexpr size_t kMaxSeen = 4;
     std::vector<std::vector<unsigned char>> seen;
@@ -1247,19 +1251,24 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
 // first call on new memory 0.42 and 0.36 ms.
 // A graph lives as long as its context: destroying one that had been
 // replayed many times without a wait, after its stream had been
-// synchronised, ended in a segmentation fault on the host.  A context that
-// holds kMaxGraphs of them runs further calls kernel by kernel.
+// synchronised, ended in a segmentation fault on the host (whose cause is not
+// known).  A context that holds kMaxGraphs of them runs further calls kernel by
+// kernel.
 // Kernel launches, event records and waits are the only stream work `body`
 // does (no memset or copy nodes).
 template <typename F>
 static int run_graph(spmesl_ctx *ctx, std::vector<unsigned char> &&key, F &&body)
 {
     hipStream_t user = ctx->stream;
+    auto launch = [&](hipGraphExec_t ex) -> int {
+        ctx->graph_left = ctx->graph_left || (ctx->graph_launched && ctx->graph_stream != user);
+        ctx->graph_launched = true;
+        ctx->graph_stream = user;
+        HIPTRY(ctx, hipGraphLaunch(ex, user));
+        return SPMESL_OK;
+    };
     for (auto &cg : ctx->graphs)
-        if (cg.key == key) {
-            HIPTRY(ctx, hipGraphLaunch(cg.exec, user));
-            return SPMESL_OK;
-        }
+        if (cg.key == key) return launch(cg.exec);
     if (ctx->graphs.size() >= spmesl_ctx::kMaxGraphs) return body();
     auto &seen = ctx->seen;
     const auto it = std::find(seen.begin(), seen.end(), key);
@@ -1288,8 +1297,7 @@ static int run_graph(spmesl_ctx *ctx, std::vector<unsigned char> &&key, F &&body
     if (ei != hipSuccess)
         return fail(ctx, SPMESL_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(ei));
     ctx->graphs.push_back(spmesl_ctx::CachedGraph{std::move(key), ex});
-    HIPTRY(ctx, hipGraphLaunch(ex, user));
-    return SPMESL_OK;
+    return launch(ex);
 }
 
 // Status of one finished solve from its control block; fills stats.
@@ -1767,16 +1775,15 @@ void spmesl_destroy(spmesl_ctx *ctx)
     if (!ctx) return;
     {
         DevGuard g(ctx->device);
+        // a graph goes only once it runs nowhere: it may have been launched on
+        // a stream the context has since left, which may be gone itself
+        if (ctx->graph_left || (ctx->graph_launched && ctx->graph_stream != ctx->stream)) (void)hipDeviceSynchronize();
         if (ctx->stream || ctx->ws) (void)hipStreamSynchronize(ctx->stream);
-        if (ctx->side) {
-            (void)hipStreamSynchronize(ctx->side);
-            (void)hipStreamDestroy(ctx->side);
-        }
+        if (ctx->side) (void)hipStreamSynchronize(ctx->side);
+        if (ctx->cap) (void)hipStreamSynchronize(ctx->cap);
         for (auto &cg : ctx->graphs) (void)hipGraphExecDestroy(cg.exec);
-        if (ctx->cap) {
-            (void)hipStreamSynchronize(ctx->cap);
-            (void)hipStreamDestroy(ctx->cap);
-        }
+        if (ctx->side) (void)hipStreamDestroy(ctx->side);
+        if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
         for (int i = 0; i < spmesl_ctx::kMaxMarks; ++i)
             if (ctx->kev[i]) (void)hipEventDestroy(ctx->kev[i]);
         if (ctx->fork) (void)hipEventDestroy(ctx->fork);
