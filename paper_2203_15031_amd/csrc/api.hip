@@ -180,7 +180,7 @@ Plan make_plan_data(int64_t n, int64_t p)
     L.dsk = b.take(8 * 16 * G * VC);
     L.svv_cap = L.dvcap;
     L.dsvv = b.take(8 * G * VC * VC);
-    L.de = b.take(8 * 16 * ((N + 31) / 32 * 32) * G);
+    L.de = b.take(8 * 16 * (size_t)dense_e_rows(n) * G);
     L.total = b.cur;
     return L;
 }
@@ -189,7 +189,8 @@ Plan make_plan_data(int64_t n, int64_t p)
 // dense workspace: the marks, V and its previous copy (p each), R, B, B_prev
 // and the screen values (16 p each) and, in the mixed form, S[V, V] and E of
 // the double stage.  G is the number of slices that fit a quarter of the
-// rest of the plan (at least 16 MB), from 1 to kDenseGroupsMax.
+// rest of the plan (at least 16 MB), from 1 to kDenseGroupsMax and to the
+// groups of 16 that p columns make.
 constexpr int kDenseGroupsMax = 32;
 constexpr size_t kDenseBudgetFloor = (size_t)16 << 20;
 Plan make_plan_g(int64_t n, int64_t p, int prec, int G);
@@ -200,9 +201,9 @@ Plan make_plan(int64_t n, int64_t p, int prec, bool data = false)
     const Plan one = make_plan_g(n, p, prec, 1);
     const size_t P = (size_t)p;
     size_t slice = 4 * P + 8 * P + 4 * 8 * 16 * P;
-    if (prec == SPMESL_MIXED) slice += 8 * (size_t)one.svv_cap * (size_t)one.svv_cap + 8 * 16 * (((size_t)n + 31) / 32 * 32);
+    if (prec == SPMESL_MIXED) slice += 8 * (size_t)one.svv_cap * (size_t)one.svv_cap + 8 * 16 * (size_t)n;
     const size_t budget = std::max(kDenseBudgetFloor, one.total / 4);
-    const int G = (int)std::min<size_t>(kDenseGroupsMax, std::max<size_t>(1, budget / slice));
+    const int G = (int)std::min<size_t>({kDenseGroupsMax, (P + 15) / 16, std::max<size_t>(1, budget / slice)});
     return G == 1 ? one : make_plan_g(n, p, prec, G);
 }
 
@@ -228,7 +229,11 @@ Plan make_plan_g(int64_t n, int64_t p, int prec, int G)
         // the statistics' partial sums (16 rchunks p bytes, rchunks at most
         // (n + 7) / 8) are read before Xt is written over them
         L.partial = L.xt;
-        L.split = b.take(2 * (size_t)split_size(p, L.npad));
+        // ... and the split by the covariance, before the dense tier writes
+        // its residuals E over it (the rows that pad the split to blocks of
+        // 16 variables cost a small p more than it holds)
+        const size_t e = 8 * 16 * (size_t)dense_e_rows(n) * (size_t)G;
+        L.split = b.take(std::max(2 * (size_t)split_size(p, L.npad), e));
     }
     L.S = b.take(tsz * P * P);
     // per-column lists hold kWMax entries each; the dense tier's longer
@@ -276,7 +281,7 @@ Plan make_plan_g(int64_t n, int64_t p, int prec, int G)
         // S[V, V] of the double dense tier (formed from the data)
         L.svv_cap = p < kDenseDataMax ? p : kDenseDataMax;
         L.dsvv = b.take(8 * (size_t)L.svv_cap * (size_t)L.svv_cap * GG);
-        L.de = b.take(8 * 16 * ((N + 31) / 32 * 32) * GG);
+        L.de = L.split;
         L.sigma64 = b.take(8 * P);
         L.lam64 = b.take(8 * P);
         L.cstat64 = b.take(4 * P);

@@ -332,6 +332,14 @@ struct DenseSrc {
     const int *pend_cnt;  // [p] extra candidates (kPendMax per column), or null
     const int *pend_idx;
 };
+// Rows in memory of the residuals E (samples x 16) of a data source's full
+// gradient: whole rounds of 16 samples, none where they fit the kernel's LDS.
+constexpr int64_t kDenseELds = 768;
+__host__ __device__ inline int64_t dense_e_rows(int64_t n)
+{
+    return n <= kDenseELds ? 0 : (n + 15) / 16 * 16;
+}
+
 // ... and what the tier needs and writes.
 template <typename T>
 struct DenseArgs {
@@ -363,7 +371,7 @@ struct DenseArgs {
     int64_t vcap;         // the most rows V may hold (a group beyond it fails)
     double *Svv;          // [svv_cap^2] per slice (data source)
     int64_t svv_cap;
-    double *E;            // [16 * (n rounded up to 32)] per slice (data source)
+    double *E;            // [16 * dense_e_rows(n)] per slice (data source)
     unsigned long long *counters;
     const int *flags;
 };

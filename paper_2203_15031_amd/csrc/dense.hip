@@ -195,6 +195,7 @@ constexpr int kBMax = 64;    // rows per block at most (one lane each)
 // same memory holds the residuals E of the data source's full gradient
 constexpr int kVLds = 384;
 template <typename T> constexpr size_t dense_lds_bytes() { return 2 * (size_t)kVLds * kDW * sizeof(T); }
+static_assert(kDenseELds * kDW * sizeof(double) <= dense_lds_bytes<double>() && kDenseELds % 16 == 0, "E in LDS");
 
 enum : int { kDSweep = 0, kDDone = 1, kDFail = 2 };
 
@@ -419,7 +420,7 @@ __device__ __forceinline__ void kkt_all(const DenseArgs<T> &A, DenseSm<T> &sm, i
         const double *Xt = A.Xt;
         const int tn = (int)((n + 15) / 16);
         const int nch = (int)((n + 15) / 16);  // chunks of 16 samples
-        const bool in_lds = (size_t)nch * 16 * kDW * sizeof(double) <= dense_lds_bytes<double>();
+        const bool in_lds = dense_e_rows(n) == 0;
         // within 8 samples the even ones come first: the order the pairs of
         // a row of the data are multiplied in
         auto epos = [](int64_t k) { return (k & ~(int64_t)7) | ((k & 1) << 2) | ((k >> 1) & 3); };
@@ -904,7 +905,7 @@ __device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const Dense
         A.sk += bi * vc * kDW;
         if (DATA) {
             A.Svv += bi * A0.svv_cap * A0.svv_cap;
-            A.E += bi * (int64_t)kDW * ((A0.n + 31) / 32 * 32);
+            A.E += bi * kDW * dense_e_rows(A0.n);
         }
     }
     // V may hold vcap rows (and, from the data, svv_cap)
