@@ -35,7 +35,7 @@ struct Ctl {
     int esc_c;        // escalations of the flagged columns' re-solves
     int esc_polish;   // escalations of the polish
     int dense;        // columns handed to the dense tier
-    int dense64;      // columns handed to the dense tier by the polish
+    int dense64;      // columns handed to the dense tier by the polish, or the data form's groups put off
     int pool;         // pool entries taken by the dense tier's results
     int pool64;
     int pad[1];
@@ -105,6 +105,14 @@ int fill_split_for(const spmesl_tuning &t, int prec, int64_t cells)
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Slices of the data form's dense workspace: places in the workspace of the
+// arrays of `groups` workgroups whose V holds up to vcap rows.
+struct DenseSlices {
+    int groups = 0;
+    int64_t vcap = 0;
+    size_t mark, v, vold, r, bd, bp, sk, svv, e, end;
+};
+
 struct Plan {
     int64_t n = 0, p = 0, npad = 0;
     int prec = 0, rchunks = 1;
@@ -115,13 +123,14 @@ struct Plan {
     // the dense tier: queues, result offsets into the pools, workspace
     size_t dq, dq64, woff, woff64, dmark, dv, dvold, dr, dbd, dbp, dsk, dsvv, de;
     int64_t pool_cap = 0, svv_cap = 0;
-    // the data form (no S): workgroups of its dense tier and rows of V each
+    // the data form (no S): its dense tier's slices, for every V and (none: no
+    // workgroups) for many workgroups with a smaller one; the groups put off
     bool data = false;
-    int dgroups = 1;
+    DenseSlices dfull, dmany;
+    size_t dputoff = 0;
     // workgroups of the S forms' dense tiers (each with its own slice of
     // the dense workspace)
     int sgroups = 1;
-    int64_t dvcap = 0;
     size_t total = 0;
 };
 
@@ -136,10 +145,41 @@ struct Bump {
 };
 
 // The data form (SPMESL_FLAG_DATA_FORM, double): no S.  The standardised
-// data Xt, the per-column lists, and the dense tier's workspace for
-// kDataGroups workgroups whose V holds up to kDataVcap rows.
-constexpr int kDataGroups = 256;
-constexpr int64_t kDataVcap = 1024;  // V beyond it fails (S_VV of 8 MB per workgroup)
+// data Xt, the per-column lists, and the dense tier's workspace: slices of
+// kDataGroups workgroups whose V holds up to kDataVcap rows (S_VV of 8 MB
+// each), 1.1 GB and the larger part of it.  Where the columns make more groups
+// than that, the same memory is first cut for up to kDataGroupsMany workgroups,
+// one per CU, of as many rows as fit then (p = 2500: 157 of 928 rows, p from
+// 4096: 256 of 704-720), and the groups that outgrow those, which are rare
+// (kDataVMany and more rows), are put off to a second launch on the full
+// slices.  n = 400, p = 2500 (157 groups, V about 40): one round of 1.33 ms
+// where 128 workgroups take two; the second launch, which finds nothing put
+// off, 4 us (slices of 8 MB for every workgroup, 1.4 to 2.3 GB, do without).
+constexpr int kDataGroups = 128;
+constexpr int64_t kDataVcap = 1024;  // V beyond it fails
+constexpr int kDataGroupsMany = 256;
+constexpr int64_t kDataVMany = 256;  // (fewer rows than this are not worth it)
+
+DenseSlices data_slices(size_t base, int64_t n, int64_t p, int64_t groups, int64_t vcap)
+{
+    DenseSlices d;
+    d.groups = (int)groups;
+    d.vcap = vcap;
+    const size_t P = (size_t)p, G = (size_t)groups, VC = (size_t)vcap;
+    Bump b;
+    b.cur = base;
+    d.mark = b.take(4 * G * P);
+    d.v = b.take(4 * G * VC);
+    d.vold = b.take(4 * G * VC);
+    d.r = b.take(8 * 16 * G * VC);
+    d.bd = b.take(8 * 16 * G * VC);
+    d.bp = b.take(8 * 16 * G * VC);
+    d.sk = b.take(8 * 16 * G * VC);
+    d.svv = b.take(8 * G * VC * VC);
+    d.e = b.take(8 * 16 * (size_t)dense_e_rows(n) * G);
+    d.end = b.cur;
+    return d;
+}
 
 Plan make_plan_data(int64_t n, int64_t p)
 {
@@ -152,9 +192,6 @@ Plan make_plan_data(int64_t n, int64_t p)
     L.npad = (n + 63) / 64 * 64;
     const size_t P = (size_t)p, N = (size_t)n;
     const int64_t groups = (p + 15) / 16;
-    L.dgroups = (int)(groups < kDataGroups ? groups : kDataGroups);
-    L.dvcap = p < kDataVcap ? p : kDataVcap;
-    const size_t G = (size_t)L.dgroups, VC = (size_t)L.dvcap;
     Bump b;
     L.mean = b.take(8 * P);
     L.scale = b.take(8 * P);
@@ -171,16 +208,15 @@ Plan make_plan_data(int64_t n, int64_t p)
     L.cstat = b.take(4 * P);
     L.colinfo = b.take(16 * P);
     L.pendcnt = b.take(4 * P);
-    L.dmark = b.take(4 * G * P);
-    L.dv = b.take(4 * G * VC);
-    L.dvold = b.take(4 * G * VC);
-    L.dr = b.take(8 * 16 * G * VC);
-    L.dbd = b.take(8 * 16 * G * VC);
-    L.dbp = b.take(8 * 16 * G * VC);
-    L.dsk = b.take(8 * 16 * G * VC);
-    L.svv_cap = L.dvcap;
-    L.dsvv = b.take(8 * G * VC * VC);
-    L.de = b.take(8 * 16 * (size_t)dense_e_rows(n) * G);
+    L.dputoff = b.take(4 * (size_t)groups);
+    L.dfull = data_slices(b.cur, n, p, std::min<int64_t>(groups, kDataGroups), std::min(p, kDataVcap));
+    if (groups > kDataGroups) {
+        const int64_t many = std::min<int64_t>(groups, kDataGroupsMany);
+        int64_t vc = kDataVcap;
+        while (vc >= kDataVMany && data_slices(b.cur, n, p, many, vc).end > L.dfull.end) vc -= 16;
+        if (vc >= kDataVMany) L.dmany = data_slices(b.cur, n, p, many, vc);
+    }
+    b.cur = L.dfull.end;
     L.total = b.cur;
     return L;
 }
@@ -1159,7 +1195,8 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
     Marker marker(ctx);
     Marker *mk = ev ? &marker : nullptr;
     mark(mk, s, nullptr);
-    launch_zero_words((uint32_t *)dctl, sizeof(Ctl) / 4, s);
+    // (the per-column counters start at zero: the tier adds to them)
+    launch_zero_start((uint32_t *)dctl, sizeof(Ctl) / 4, FillJob{(double *)(ws + L.colinfo), 2 * p}, FillJob{}, s);
     mark(mk, s, "zero_control");
     if (!launch_stats_split(make_split_job(L, prob, ws, dctl), s)) {
         launch_colstats(prob->X, n, p, prob->ldx, (double *)(ws + L.partial), L.rchunks, mean, scale,
@@ -1208,17 +1245,6 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
     d.band_cnt = nullptr;
     d.info = (int *)(ws + L.colinfo);
     d.info_stride = 4;
-    d.mark = (int *)(ws + L.dmark);
-    d.V = (int *)(ws + L.dv);
-    d.Vold = (int *)(ws + L.dvold);
-    d.R = (double *)(ws + L.dr);
-    d.Bd = (double *)(ws + L.dbd);
-    d.Bp = (double *)(ws + L.dbp);
-    d.sk = (double *)(ws + L.dsk);
-    d.vcap = L.dvcap;
-    d.Svv = (double *)(ws + L.dsvv);
-    d.svv_cap = L.svv_cap;
-    d.E = (double *)(ws + L.de);
     d.counters = dctl->counters;
     d.flags = &dctl->flags;
     DenseSrc<double> src{};
@@ -1229,9 +1255,22 @@ static int enqueue_data_form(spmesl_ctx *ctx, const spmesl_problem *prob, const 
         src.off = d.w_off;
         src.sigma = d.sigma;
     }
-    // the per-column counters start at zero (the tier adds to them)
-    launch_zero_words((uint32_t *)(ws + L.colinfo), 4 * p, s);
-    launch_dense<double, double>(d, src, s, L.dgroups);
+    auto run = [&](const DenseSlices &z, const DensePutOff &po) {
+        d.mark = (int *)(ws + z.mark);
+        d.V = (int *)(ws + z.v);
+        d.Vold = (int *)(ws + z.vold);
+        d.R = (double *)(ws + z.r);
+        d.Bd = (double *)(ws + z.bd);
+        d.Bp = (double *)(ws + z.bp);
+        d.sk = (double *)(ws + z.sk);
+        d.vcap = d.svv_cap = z.vcap;
+        d.Svv = (double *)(ws + z.svv);
+        d.E = (double *)(ws + z.e);
+        launch_dense<double, double>(d, src, s, z.groups, po);
+    };
+    int *const putoff = (int *)(ws + L.dputoff), *const nputoff = &dctl->dense64;
+    if (L.dmany.groups) run(L.dmany, DensePutOff{putoff, nputoff, nullptr, nullptr});
+    run(L.dfull, L.dmany.groups ? DensePutOff{nullptr, nullptr, putoff, nputoff} : DensePutOff{});
     mark(mk, s, "dense_data_form");
     if (ev) HIPTRY(ctx, hipEventRecord(ev[3], s));
     if (ev) HIPTRY(ctx, hipEventRecord(ev[4], s));

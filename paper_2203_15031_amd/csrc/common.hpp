@@ -375,8 +375,17 @@ struct DenseArgs {
     unsigned long long *counters;
     const int *flags;
 };
+// The data form's two launches: the first puts the groups whose V outgrows its
+// slices off to a list (put, counted in nput; null: such a group fails), the
+// second takes the groups of that list (take, of which there are *ntake; null:
+// every group of the queue).
+struct DensePutOff {
+    int *put, *nput;
+    const int *take, *ntake;
+};
 template <typename T, typename TS>
-void launch_dense(const DenseArgs<T> &a, const DenseSrc<TS> &src, hipStream_t s, int blocks = 1);
+void launch_dense(const DenseArgs<T> &a, const DenseSrc<TS> &src, hipStream_t s, int blocks = 1,
+                  const DensePutOff &po = {});
 // Many problems' queues in one launch (the workgroups of problem d are off[d] ..).
 template <typename T, typename TS>
 struct DenseJob {

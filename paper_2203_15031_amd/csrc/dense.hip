@@ -216,9 +216,10 @@ struct DenseSm {
 };
 
 // Block-wide compaction of the rows marked in `mark` (in ascending order)
-// into V; every marked row becomes 1.  Returns |V|.
+// into V; every marked row becomes 1.  Returns |V|, of which at most `cap`
+// entries are written.
 template <typename T>
-__device__ __forceinline__ int compact_v(const DenseArgs<T> &A, DenseSm<T> &sm)
+__device__ __forceinline__ int compact_v(const DenseArgs<T> &A, DenseSm<T> &sm, int64_t cap)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     int base = 0;
@@ -234,7 +235,8 @@ __device__ __forceinline__ int compact_v(const DenseArgs<T> &A, DenseSm<T> &sm)
             tot += sm.scan[w];
         }
         if (f) {
-            A.V[off + lanes_below(m)] = (int)j;
+            const int at = off + lanes_below(m);
+            if (at < cap) A.V[at] = (int)j;
             A.mark[j] = 1;
         }
         base += tot;
@@ -252,11 +254,11 @@ __device__ __forceinline__ int compact_v(const DenseArgs<T> &A, DenseSm<T> &sm)
 template <typename T>
 __device__ __forceinline__ int build_v(const DenseArgs<T> &A, DenseSm<T> &sm, int64_t cap)
 {
-    const int nv = compact_v(A, sm);
+    const int nv = compact_v(A, sm, cap);
     if (nv >= A.pv || A.pv > cap || 16 * (int64_t)nv < 15 * A.pv) return nv;
     for (int64_t j = threadIdx.x; j < A.pv; j += kDT) A.mark[j] = 1;
     __syncthreads();
-    return compact_v(A, sm);
+    return compact_v(A, sm, cap);
 }
 
 // position of row j in V[0 .. nv) (j is in V)
@@ -881,17 +883,20 @@ __device__ __forceinline__ void iterate(const DenseArgs<T> &A, DenseSm<T> &sm, i
     __syncthreads();
 }
 
-// Workgroup bi of nb takes the queue's groups bi, bi + nb, ..
+// Workgroup bi of nb takes the groups bi, bi + nb, .. of the queue (or of
+// po.take).
 template <typename T, typename TS, bool DATA>
 __device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const DenseSrc<TS> &src, DenseSm<T> &sm, T *lds,
-                                             int64_t bi, int64_t nb)
+                                             int64_t bi, int64_t nb, const DensePutOff &po)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    if (po.take && bi >= *po.ntake) return;  // (the rule: nothing was put off)
     if (*A0.flags) return;
     const int64_t p = A0.p;
     // the queue, or (no queue) the columns 0 .. ncols - 1
     const int q = A0.queue ? *A0.qcnt : (int)A0.ncols;
-    if (q <= 0 || bi * kDW >= q) return;
+    const int ng = po.take ? *po.ntake : (q + kDW - 1) / kDW;
+    if (bi >= ng) return;
     // this workgroup's slice of the workspace
     DenseArgs<T> A = A0;
     {
@@ -913,7 +918,8 @@ __device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const Dense
     for (int64_t j = tid; j < p; j += kDT) A.mark[j] = 0;
     __syncthreads();
     const int b = A.block <= 16 ? 16 : (A.block <= 32 ? 32 : kBMax);
-    for (int g0 = (int)bi * kDW; g0 < q; g0 += (int)nb * kDW) {
+    for (int gi = (int)bi; gi < ng; gi += (int)nb) {
+        const int g0 = (po.take ? po.take[gi] : gi) * kDW;
         const int m = q - g0 < kDW ? q - g0 : kDW;
         // --- the group's columns and their start --------------------------
         if (tid < kDW) {
@@ -955,7 +961,8 @@ __device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const Dense
         int nv = build_v(A, sm, vlim);
         bool gfail = false;
         if ((int64_t)nv > vlim) {
-            // V does not fit this workgroup's buffers: the group fails (rare)
+            // V does not fit this workgroup's buffers: the group fails, or is
+            // put off (rare)
             if (tid < m) sm.status[tid] = kColWorkset, sm.state[tid] = kDFail;
             gfail = true;
             nv = 0;
@@ -1034,8 +1041,13 @@ __device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const Dense
             __syncthreads();
             if (gfail) break;
         }
+        if (gfail) {  // (V does not hold every mark)
+            if (tid == 0 && po.put) po.put[atomicAdd(po.nput, 1)] = g0 / kDW;
+            for (int64_t j = tid; j < p; j += kDT) A.mark[j] = 0;
+            __syncthreads();
+        }
         // --- results: the nonzeros of each column, ascending ---------------
-        for (int c = wv; c < m; c += kNW) {
+        for (int c = wv; c < m && !(gfail && po.put); c += kNW) {
             const int64_t k = sm.ck[c];
             int cnt = 0;
             for (int v0 = 0; v0 < nv; v0 += kWave) {
@@ -1099,11 +1111,11 @@ __device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const Dense
 }
 
 template <typename T, typename TS, bool DATA>
-__global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src)
+__global__ __launch_bounds__(kDT) void k_dense(DenseArgs<T> A0, DenseSrc<TS> src, DensePutOff po)
 {
     __shared__ DenseSm<T> sm;
     extern __shared__ __align__(16) unsigned char dense_lds[];
-    dense_groups<T, TS, DATA>(A0, src, sm, reinterpret_cast<T *>(dense_lds), blockIdx.x, gridDim.x);
+    dense_groups<T, TS, DATA>(A0, src, sm, reinterpret_cast<T *>(dense_lds), blockIdx.x, gridDim.x, po);
 }
 
 // block b is workgroup b - off[d] of problem d
@@ -1116,21 +1128,21 @@ __global__ __launch_bounds__(kDT) void k_dense_grouped(const DenseJob<T, TS> *__
     const int64_t b = blockIdx.x;
     const int d = group_of(off, nd, b);
     dense_groups<T, TS, DATA>(tab[d].a, tab[d].src, sm, reinterpret_cast<T *>(dense_lds), b - off[d],
-                              off[d + 1] - off[d]);
+                              off[d + 1] - off[d], DensePutOff{});
 }
 
 } // namespace
 
 template <typename T, typename TS>
-void launch_dense(const DenseArgs<T> &a, const DenseSrc<TS> &src, hipStream_t s, int blocks)
+void launch_dense(const DenseArgs<T> &a, const DenseSrc<TS> &src, hipStream_t s, int blocks, const DensePutOff &po)
 {
     if constexpr (sizeof(T) == 8) {
         if (a.Xt) {
-            hipLaunchKernelGGL((k_dense<T, TS, true>), dim3(blocks), dim3(kDT), dense_lds_bytes<T>(), s, a, src);
+            hipLaunchKernelGGL((k_dense<T, TS, true>), dim3(blocks), dim3(kDT), dense_lds_bytes<T>(), s, a, src, po);
             return;
         }
     }
-    hipLaunchKernelGGL((k_dense<T, TS, false>), dim3(blocks), dim3(kDT), dense_lds_bytes<T>(), s, a, src);
+    hipLaunchKernelGGL((k_dense<T, TS, false>), dim3(blocks), dim3(kDT), dense_lds_bytes<T>(), s, a, src, po);
 }
 
 template <typename T, typename TS>
@@ -1148,8 +1160,11 @@ template void launch_dense_grouped<float, float>(const DenseJob<float, float> *,
                                                  hipStream_t);
 template void launch_dense_grouped<double, float>(const DenseJob<double, float> *, const int64_t *, int, int64_t,
                                                   hipStream_t);
-template void launch_dense<double, double>(const DenseArgs<double> &, const DenseSrc<double> &, hipStream_t, int);
-template void launch_dense<float, float>(const DenseArgs<float> &, const DenseSrc<float> &, hipStream_t, int);
-template void launch_dense<double, float>(const DenseArgs<double> &, const DenseSrc<float> &, hipStream_t, int);
+template void launch_dense<double, double>(const DenseArgs<double> &, const DenseSrc<double> &, hipStream_t, int,
+                                          const DensePutOff &);
+template void launch_dense<float, float>(const DenseArgs<float> &, const DenseSrc<float> &, hipStream_t, int,
+                                          const DensePutOff &);
+template void launch_dense<double, float>(const DenseArgs<double> &, const DenseSrc<float> &, hipStream_t, int,
+                                          const DensePutOff &);
 
 } // namespace spmesl

@@ -24,3 +24,11 @@ def _size(n, p, prec, data_form=False):
                                  (7372, 500), (3648, 1000), (1912, 1500), (1024, 2048), (735, 2300)])
 def test_noalloc_still_holds(n, p):
     assert _size(n, p, "mixed") <= NOALLOC
+
+
+# the data form's, with the slices of 128 workgroups: more workgroups share them
+@pytest.mark.parametrize("n,p,size", [(400, 2048, 1166213296), (400, 2500, 1169961648), (60, 4096, 1157431472),
+                                      (400, 5000, 1190681264), (33, 20000, 1205147056),
+                                      (2000, 100000, 3853854384), (50, 1000000, 4311505072)])
+def test_data_form_workspace(n, p, size):
+    assert _size(n, p, "fp64", data_form=True) <= size
