@@ -149,8 +149,8 @@ struct Bump {
 // kDataGroups workgroups whose V holds up to kDataVcap rows (S_VV of 8 MB
 // each), 1.1 GB and the larger part of it.  Where the columns make more groups
 // than that, the same memory is first cut for up to kDataGroupsMany workgroups,
-// one per CU, of as many rows as fit then (p = 2500: 157 of 928 rows, p from
-// 4096: 256 of 704-720), and the groups that outgrow those, which are rare
+// one per CU, of as many rows as fit then (p = 2500: 157 of 912 rows, p from
+// 4096: 256 of 704), and the groups that outgrow those, which are rare
 // (kDataVMany and more rows), are put off to a second launch on the full
 // slices.  n = 400, p = 2500 (157 groups, V about 40): one round of 1.33 ms
 // where 128 workgroups take two; the second launch, which finds nothing put
