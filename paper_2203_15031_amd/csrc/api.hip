@@ -1382,8 +1382,9 @@ static int decode(const Ctl &c, int64_t p, spmesl_stats *st)
 // offsets of each problem's items), so that small problems and the slow
 // columns of each fill the chip together instead of one problem's tail at a
 // time (16 hub networks with the standardisation, fills, dense tier,
-// statistics and scatter per problem, 4-12 us a launch: 1.16 ms; now 0.88).  Each problem keeps its own workspace region and control block; a
-// column's arithmetic is that of the single solve.
+// statistics and scatter per problem, 4-12 us a launch: 1.16 ms; grouped 0.88).
+// Each problem keeps its own workspace region and control block; a column's
+// arithmetic is that of the single solve.
 // ---------------------------------------------------------------------------
 struct BatchTabs {
     // uploaded from the host: the tables and the host-known offsets

@@ -49,9 +49,10 @@
 //     updates 10.9 -> 6.1 ms, the solve 15.9 -> 11.6 ms, 8.5 with the LDS
 //     tiers' shorter steps, and 6.5 with blocks of 64 rows (of 32: 7.3, of 16:
 //     10.2; half the barriers, each waiting for its slowest column);
-//   n = 400, p = 2500, data form (157 groups, V about 40): 6.0 -> 1.2 ms a
-//     solve: a group's iterations 450 -> 40 us, a full gradient 870 -> 290 us
-//     (its 2 GB of Xt reads a pass come from the caches at 4.4 TB/s).
+//   n = 400, p = 2500, data form (157 groups, V about 40): 6.0 -> 1.1 to 1.3 ms
+//     a solve, by the box: a group's iterations 450 -> 40 us, a full gradient
+//     870 -> 290 us (its 2 GB of Xt reads a pass come from the caches at 4.4
+//     TB/s).
 #include <type_traits>
 
 #include "colsolve_dev.hpp"
