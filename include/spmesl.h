@@ -313,9 +313,9 @@ int spmesl_get_tuning(const spmesl_ctx *ctx, spmesl_tuning *t);
  * 700/800/900/1000, KKT rows 4/2/1 as they fit, fill 32/64/128/256
  * workgroups, fill placement 0/1/2, dense block 16/32/64 when the problem
  * reaches the dense tier).  The shapes found are then timed against the
- * defaults as repeated calls run them (graph replays; at most two of the
- * context's graphs), and the defaults are kept unless they are at least 1%
- * slower.  Sets the result on the context and writes it to *best (host,
+ * defaults as repeated calls run them (graph replays; with the last solve's
+ * at most three of the context's graphs), and the defaults are kept unless
+ * they are at least 1% slower.  Sets the result on the context and writes it to *best (host,
  * may be NULL) with its time per solve in *ms_best (host, may be NULL).  The
  * outputs in `res` hold the last solve's result.  Allocates (workspace,
  * graphs, a status word).  Returns SPMESL_OK or the first error of a solve. */

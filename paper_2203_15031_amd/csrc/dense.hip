@@ -891,7 +891,7 @@ __device__ __forceinline__ void dense_groups(const DenseArgs<T> &A0, const Dense
                                              int64_t bi, int64_t nb, const DensePutOff &po)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-    if (po.take && bi >= *po.ntake) return;  // (the rule: nothing was put off)
+    if (po.take && bi >= *po.ntake) return;  // (as a rule nothing was put off)
     if (*A0.flags) return;
     const int64_t p = A0.p;
     // the queue, or (no queue) the columns 0 .. ncols - 1
